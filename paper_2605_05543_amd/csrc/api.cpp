@@ -24,8 +24,7 @@ hipError_t launch_pair_fp64(const PairParams &p, hipStream_t stream, bool kstar,
 hipError_t launch_pair_mixed(const PairParams &p, hipStream_t stream, bool kstar, bool count);
 hipError_t launch_lightcone_records(const double4 *ring_w, const double *T, int64_t N, int D, int head,
                                     double4 *rec, hipStream_t s);
-hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, const int32_t *order, double *E,
-                               double *B, hipStream_t s);
+hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, hipStream_t s);
 hipError_t launch_push(const PushParams &p, hipStream_t s);
 hipError_t launch_init_straight(double4 *rw, double4 *rv, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s);
@@ -794,7 +793,6 @@ empp_status empp_step(empp_ctx *ctx, int64_t nsteps)
         q.eps = ctx->cfg.q * ctx->cfg.dt / (2.0 * ctx->cfg.m);
         q.ext_field = ctx->cfg.ext_field;
         q.dip_k = ctx->cfg.dipole_b0 * ctx->cfg.dipole_re * ctx->cfg.dipole_re * ctx->cfg.dipole_re;
-        q.self_field = 1;
         if (ctx->cfg.adaptive) {
             q.ad = slot;
             q.ad_next = other;
@@ -874,7 +872,7 @@ static empp_status fields_dev_impl(empp_ctx *ctx, int64_t m, const double *x_dev
             Ec = (double *)obuf.ptr;
             Bc = Ec + 3 * mc;
         }
-        HIP_TRY(launch_merge_fields(ctx->part(), ctx->nsplit, mc, nullptr, Ec, Bc, ctx->stream));
+        HIP_TRY(launch_merge_fields(ctx->part(), ctx->nsplit, mc, Ec, Bc, ctx->stream));
         if (m > N) {
             for (int k = 0; k < 3; ++k) {
                 HIP_TRY(hipMemcpyAsync(E_dev + k * m + a0, Ec + k * mc, mc * sizeof(double), hipMemcpyDeviceToDevice,
@@ -954,7 +952,7 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
                                              : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
     if (e != hipSuccess)
         return fail(EMPP_EDEVICE, "pair pass: %s", hipGetErrorString(e));
-    HIP_TRY(launch_merge_fields(p.part, ctx->nsplit, m, nullptr, E_dev, B_dev, ctx->stream));
+    HIP_TRY(launch_merge_fields(p.part, ctx->nsplit, m, E_dev, B_dev, ctx->stream));
     return EMPP_OK;
 }
 

@@ -102,7 +102,7 @@ struct PushParams {
     double4 *ring_v;
     double *T;
     double *u;          // [3][N]
-    double *E;          // [3][N] self-field of the step (output of the merge)
+    double *E;          // [3][N] self-field of the step (written by the merge)
     double *B;
     const double *part; // [nsplit][12][N], in the pair launch's target order
     const int32_t *order; // target order -> particle index
@@ -116,7 +116,6 @@ struct PushParams {
     double eps;         // q dt / (2 m)
     int32_t ext_field;
     double dip_k;       // b0 * re^3: (mu0/4pi) M0 for the centred dipole
-    int32_t self_field; // 0: stage-II transport (E = 0, B = B_geo only)
     // adaptive step: ad = this step's {eta_min, v_max^2} slot (null: fixed
     // dt); the step is c_dt eta_min / v_max clamped to [dt_min, dt_max],
     // t_now is read from T[head], and ad_next/dt_out are reset/written
