@@ -22,14 +22,13 @@ namespace empp {
 int pair_fp64_tile(int D);
 hipError_t launch_pair_fp64(const PairParams &p, hipStream_t stream, bool kstar, bool count);
 hipError_t launch_pair_mixed(const PairParams &p, hipStream_t stream, bool kstar, bool count);
-hipError_t launch_lightcone_records(const double4 *ring_w, const double *T, int64_t N, int D, int head,
-                                    double4 *rec, hipStream_t s);
+hipError_t launch_segments(const double4 *ring_v, int64_t N, int D, double4 *seg, hipStream_t s);
 hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, hipStream_t s);
 hipError_t launch_push(const PushParams &p, hipStream_t s);
-hipError_t launch_init_straight(double4 *rw, double4 *rv, double *T, const double *r, const double *u, int64_t N,
+hipError_t launch_init_straight(double4 *rw, double4 *rv, double4 *seg, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s);
 hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, double4 *rv,
-                                  int64_t N, int D, hipStream_t s);
+                                  double4 *seg, int64_t N, int D, hipStream_t s);
 hipError_t launch_ring_to_history(const double4 *rw, const double4 *rv, double *w, double *v, int64_t N, int D,
                                   int head, hipStream_t s);
 hipError_t launch_newest_positions(const double4 *rw, double *r, int64_t N, int D, int head, hipStream_t s);
@@ -87,18 +86,9 @@ constexpr uint64_t kAlign = 256;
 uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    uint64_t ring_w, ring_v, rec, T, u, E, B, part, err, counters, diag, order, pos, skey, st, ad, kc, kc_bytes, total;
+    uint64_t ring_w, ring_v, seg, T, u, E, B, part, err, counters, diag, order, pos, skey, st, ad, kc, kc_bytes, total;
 };
 
-int tile_for_depth(int D) { return pair_fp64_tile(D); }
-
-int bisection_steps(int D)
-{
-    int nit = 0;
-    while ((1 << nit) < D - 1)
-        ++nit;
-    return nit;
-}
 
 // Spatial (Morton, 21 bits per axis) order of points x[3][N]: the pair
 // kernels visit targets in this order so that the lanes of a wavefront are
@@ -151,7 +141,7 @@ int splits_for(const empp_config &c)
     // chunks); the warm-started search, with less work per tile, does best
     // with half as many.
     int64_t bx = (c.n + kBlockFp64 - 1) / kBlockFp64;
-    int tile = tile_for_depth(c.depth);
+    const int tile = std::min(4, std::max(1, 2048 / c.depth));
     const int64_t target = c.guess == EMPP_GUESS_PREVIOUS ? 4096 : 8192;
     int64_t want = (target + bx - 1) / bx;
     int64_t maxs = std::max<int64_t>(1, c.n / (4 * tile));
@@ -171,8 +161,8 @@ Layout layout_for(const empp_config &c)
     };
     L.ring_w = take(N * D * sizeof(double4));
     L.ring_v = take(N * D * sizeof(double4));
-    // light-cone records of the present pass (lightcone_records_kernel)
-    L.rec = take(N * D * sizeof(double4));
+    // segment records (acceleration, c^2 - v^2) of every slot
+    L.seg = take(N * D * sizeof(double4));
     L.T = take(D * sizeof(double));
     L.u = take(3 * N * sizeof(double));
     L.E = take(3 * N * sizeof(double));
@@ -296,7 +286,7 @@ struct empp_ctx {
     Tp *at(uint64_t off) const { return reinterpret_cast<Tp *>(ws + off); }
     double4 *ring_w() const { return at<double4>(L.ring_w); }
     double4 *ring_v() const { return at<double4>(L.ring_v); }
-    double4 *rec() const { return at<double4>(L.rec); }
+    double4 *seg() const { return at<double4>(L.seg); }
     double *T() const { return at<double>(L.T); }
     double *u() const { return at<double>(L.u); }
     double *E() const { return at<double>(L.E); }
@@ -366,7 +356,7 @@ PairParams pair_params(empp_ctx *ctx)
     PairParams p{};
     p.ring_w = ctx->ring_w();
     p.ring_v = ctx->ring_v();
-    p.rec = ctx->rec();
+    p.seg = ctx->seg();
     p.T = ctx->T();
     p.n_src = ctx->cfg.n;
     p.D = ctx->cfg.depth;
@@ -378,7 +368,7 @@ PairParams pair_params(empp_ctx *ctx)
     p.nsplit = ctx->nsplit;
     p.src_per_split = (ctx->cfg.n + ctx->nsplit - 1) / ctx->nsplit;
     p.tile = ctx->tile;
-    p.nit = bisection_steps(ctx->cfg.depth);
+    p.sg_log2 = 0;
     p.order = nullptr;
     p.part = ctx->part();
     p.err = ctx->err();
@@ -491,33 +481,13 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
     });
 }
 
-// Whether the pair launch for p runs a search mode that stages the
-// precomputed light-cone records (the midpoint ablation and a cold warm
-// start run the bisection).
-bool pair_needs_records(const PairParams &p)
-{
-    if (p.recon == 1)
-        return false;
-    if (p.guess == EMPP_GUESS_PREVIOUS)
-        return !p.kc_cold;
-    return pass_uses_records(p.guess);
-}
-
 hipError_t launch_pair(empp_ctx *ctx, PairParams &p, bool kstar, float *G_pair = nullptr,
                        double3 *cent_pair = nullptr)
 {
     hipError_t eg = launch_guesses(ctx, p, G_pair, cent_pair);
     if (eg != hipSuccess)
         return eg;
-    // the pass's light-cone records (guided searches), then the pair kernel
-    // (timed together)
     return timed(ctx, 0, [&]() {
-        if (pair_needs_records(p)) {
-            hipError_t e = launch_lightcone_records(p.ring_w, p.T, p.n_src, p.D, p.head,
-                                                    const_cast<double4 *>(p.rec), ctx->stream);
-            if (e != hipSuccess)
-                return e;
-        }
         if (ctx->cfg.precision == EMPP_MIXED)
             return launch_pair_mixed(p, ctx->stream, kstar, ctx->counting);
         return launch_pair_fp64(p, ctx->stream, kstar, ctx->counting);
@@ -559,7 +529,7 @@ empp_status empp_create(const empp_config *cfg, empp_ctx **out)
     ctx->cfg = *cfg;
     ctx->L = layout_for(*cfg);
     ctx->nsplit = splits_for(*cfg);
-    ctx->tile = tile_for_depth(cfg->depth);
+    ctx->tile = pair_fp64_tile(cfg->depth);
     ctx->stream = (hipStream_t)cfg->stream;
     if ((st = set_device(ctx)) != EMPP_OK) {
         delete ctx;
@@ -655,7 +625,7 @@ empp_status empp_init_history_straight(empp_ctx *ctx)
     double *r_dev = ctx->part();
     HIP_TRY(hipMemcpyAsync(r_dev, ctx->r0.data(), 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipMemcpyAsync(ctx->u(), ctx->u0.data(), 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(launch_init_straight(ctx->ring_w(), ctx->ring_v(), ctx->T(), r_dev, ctx->u(), N, D, ctx->t_origin,
+    HIP_TRY(launch_init_straight(ctx->ring_w(), ctx->ring_v(), ctx->seg(), ctx->T(), r_dev, ctx->u(), N, D, ctx->t_origin,
                                  ctx->cfg.dt, ctx->stream));
     std::vector<int32_t> ord = morton_order(ctx->r0.data(), N);
     HIP_TRY(hipMemcpyAsync(ctx->order(), ord.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
@@ -708,7 +678,8 @@ empp_status empp_set_history(empp_ctx *ctx, int32_t nslots, const double *T, con
         HIP_TRY(hipMemcpyAsync(tmp, w, tot * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(hipMemcpyAsync(tmp + tot, v, tot * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(hipMemcpyAsync(ctx->T(), T, D * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-        HIP_TRY(launch_history_to_ring(tmp, tmp + tot, ctx->T(), ctx->ring_w(), ctx->ring_v(), N, D, ctx->stream));
+        HIP_TRY(launch_history_to_ring(tmp, tmp + tot, ctx->T(), ctx->ring_w(), ctx->ring_v(), ctx->seg(), N, D,
+                                       ctx->stream));
         HIP_TRY(hipMemcpyAsync(ctx->u(), u, 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         std::vector<int32_t> ord = morton_order(w + (uint64_t)(D - 1) * 3 * N, N);
         HIP_TRY(hipMemcpyAsync(ctx->order(), ord.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
@@ -777,6 +748,7 @@ empp_status empp_step(empp_ctx *ctx, int64_t nsteps)
         PushParams q{};
         q.ring_w = ctx->ring_w();
         q.ring_v = ctx->ring_v();
+        q.seg = ctx->seg();
         q.T = ctx->T();
         q.u = ctx->u();
         q.E = ctx->E();
@@ -942,14 +914,10 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
     p.m = m;
     p.kstar = kstar_dev;
     p.part = reinterpret_cast<double *>(ctx->scratch);
-    // launched directly: no timing events, no guess buffers; the records
-    // live in the context's workspace
-    hipError_t e = hipSuccess;
-    if (pair_needs_records(p))
-        e = launch_lightcone_records(p.ring_w, p.T, p.n_src, p.D, p.head, const_cast<double4 *>(p.rec), ctx->stream);
-    if (e == hipSuccess)
-        e = ctx->cfg.precision == EMPP_MIXED ? launch_pair_mixed(p, ctx->stream, kstar_dev != nullptr, ctx->counting)
-                                             : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
+    // launched directly: no timing events, no guess buffers
+    hipError_t e = ctx->cfg.precision == EMPP_MIXED
+                       ? launch_pair_mixed(p, ctx->stream, kstar_dev != nullptr, ctx->counting)
+                       : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
     if (e != hipSuccess)
         return fail(EMPP_EDEVICE, "pair pass: %s", hipGetErrorString(e));
     HIP_TRY(launch_merge_fields(p.part, ctx->nsplit, m, E_dev, B_dev, ctx->stream));
@@ -1786,6 +1754,11 @@ empp_status empp_load(empp_ctx *ctx, const char *path)
         st = file_to_dev(ctx, f, ctx->ring_w(), (uint64_t)N * D * sizeof(double4));
         if (st == EMPP_OK)
             st = file_to_dev(ctx, f, ctx->ring_v(), (uint64_t)N * D * sizeof(double4));
+        if (st == EMPP_OK) {
+            hipError_t e = launch_segments(ctx->ring_v(), N, D, ctx->seg(), ctx->stream);
+            if (e != hipSuccess)
+                st = fail(EMPP_EDEVICE, "segment records: %s", hipGetErrorString(e));
+        }
     }
     if (st == EMPP_OK && h.stage == 2) {
         st = file_to_dev(ctx, f, ctx->pos(), N * sizeof(double4));

@@ -31,6 +31,8 @@ constexpr int kMaxSplits = 1024;   // source chunks of one launch
 //   ring_w[j * D + p] = {x, y, z, 0}     position of source j at physical slot p
 //   ring_v[j * D + p] = {vx, vy, vz, 1/h} velocity leaving that slot and the
 //                                         inverse length of its segment (0: newest)
+//   seg[j * D + p]    = {ax, ay, az, C2}  acceleration (v_{p+1} - v_p)/h of the
+//                                         segment that starts there and c^2 - |v_p|^2
 //   T[p]                                  slot time
 // Slot p holds logical slot "back" b (0 = newest) when p = (head - b) mod D.
 // A source's whole history is one contiguous 32*D-byte block, so a block
@@ -39,7 +41,7 @@ constexpr int kMaxSplits = 1024;   // source chunks of one launch
 struct PairParams {
     const double4 *ring_w;
     const double4 *ring_v;
-    const double4 *rec;  // light-cone records [N][D], newest slot first (lightcone_records_kernel)
+    const double4 *seg;
     const double *T;
     int64_t n_src;      // sources N
     int32_t D;
@@ -52,20 +54,17 @@ struct PairParams {
     const double *x;
     const int64_t *self_index;  // external mode only, may be null
     const int32_t *order;       // step mode: target slot -> particle (spatial order), may be null
-    int32_t nit;                // bisection steps: ceil(log2(D - 1))
     int64_t m;
     int64_t src_per_split;
     int32_t nsplit;
     int32_t tile;               // sources staged per LDS tile
-    int32_t nbuf;               // LDS tile buffers (FP64 kernel: 1 or 2)
-    int32_t groups;             // groups of `tile` sources per staged tile (FP64 kernel)
+    int32_t sg_log2;            // log2 of the wavefronts that share a target's sources
     double *part;               // [nsplit][12][m] partial (sum, comp)
     int32_t *kstar;             // [m][N] or null
     unsigned long long *err;    // [2]: first failing pair, status bits
     unsigned long long *counters;  // [5] pairs, before, probes, rescues, fallbacks
     // surrogate / guided search
     int32_t guess;
-    float dt_inv_f;
     double dt;
     const float *G;             // surrogate guesses G[source * g_groups + (a >> g_shift)]
     int64_t g_groups;           // target groups of the launch
@@ -90,16 +89,10 @@ struct PairParams {
 
 constexpr uint16_t kBracketBefore = 0xFFFF;
 
-// Search modes (pair-kernel template argument) whose pass stages the
-// precomputed light-cone records of lightcone_records_kernel (the guided
-// searches, 1-3, and the warm start, 4) rather than computing them from the
-// positions while staging (the bisection, 0, and the cache-filling
-// bisection, 5).
-__host__ __device__ constexpr bool pass_uses_records(int guess) { return guess >= 1 && guess <= 4; }
-
 struct PushParams {
     double4 *ring_w;
     double4 *ring_v;
+    double4 *seg;
     double *T;
     double *u;          // [3][N]
     double *E;          // [3][N] self-field of the step (written by the merge)
@@ -178,6 +171,14 @@ __device__ inline void report_error(unsigned long long *err, int64_t a, int64_t 
     unsigned long long key = ((unsigned long long)(uint32_t)a << 32) | (uint32_t)j;
     atomicMin(&err[0], key);
     atomicOr(&err[1], bit);
+}
+
+// Segment record of a slot from its velocity record and the next newer one's.
+__device__ inline double4 segment_record(double4 v1, double4 v2)
+{
+    const double c2 = kC_LIGHT * kC_LIGHT;
+    const double C2 = __builtin_fma(-v1.x, v1.x, __builtin_fma(-v1.y, v1.y, __builtin_fma(-v1.z, v1.z, c2)));
+    return make_double4((v2.x - v1.x) * v1.w, (v2.y - v1.y) * v1.w, (v2.z - v1.z) * v1.w, C2);
 }
 
 // Reciprocal of a positive normal double: hardware estimate plus one

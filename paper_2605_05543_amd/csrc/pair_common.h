@@ -33,12 +33,18 @@ __device__ inline double offset_sq(double d0x, double d0y, double d0z)
     return __builtin_fma(d0z, d0z, R);
 }
 
-__device__ inline bool lightcone_positive(double4 rec, double d0x, double d0y, double d0z, double R0sq)
+// The sign-test value of a sample, inside the past light cone where it is
+// above |d0|^2.
+__device__ inline double lightcone_value(double4 rec, double d0x, double d0y, double d0z)
 {
     double q = __builtin_fma(d0x, rec.x, rec.w);
     q = __builtin_fma(d0y, rec.y, q);
-    q = __builtin_fma(d0z, rec.z, q);
-    return q > R0sq;
+    return __builtin_fma(d0z, rec.z, q);
+}
+
+__device__ inline bool lightcone_positive(double4 rec, double d0x, double d0y, double d0z, double R0sq)
+{
+    return lightcone_value(rec, d0x, d0y, d0z) > R0sq;
 }
 
 // Bisection of the paper: test the oldest sample first (if it is not

@@ -21,93 +21,51 @@ namespace empp {
 
 extern const bool kHaveMixed = true;
 
-template <bool KSTAR, bool COUNT, int GUESS, int S, int NIT = -1>
+template <bool KSTAR, bool COUNT, int GUESS, bool DB>
 __global__ __launch_bounds__(kBlockFp64, 4) void pair_mixed_kernel(PairParams p)
 {
-    pair_body<true, KSTAR, COUNT, GUESS, S, false, false, NIT>(p);
+    pair_body<true, KSTAR, COUNT, GUESS, false, false, DB>(p);
 }
 
 namespace {
 
-template <bool K, bool C, int G, int S, int NIT = -1>
-void launch_one(PairParams p, int staged, size_t lds, dim3 grid, hipStream_t stream)
+template <bool K, bool C, int G, bool DB>
+void launch_kernel(const PairParams &p, dim3 grid, hipStream_t stream)
 {
-    p.tile = S;
-    p.groups = staged / S;
-    if (NIT >= 0)
-        lds = pair_lds_bytes(p.D, staged, true);
-    if (lds > 65536)
-        (void)hipFuncSetAttribute((const void *)pair_mixed_kernel<K, C, G, S, NIT>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL((pair_mixed_kernel<K, C, G, S, NIT>), grid, dim3(kBlockFp64), lds, stream, p);
-}
-
-// The bisection with its halvings unrolled for the launch's depth (no
-// bracket output, no counters) where the tiles are double-buffered
-// (D <= 2048); deeper histories loop.
-void launch_plain(const PairParams &p, int staged, size_t lds, dim3 grid, hipStream_t stream)
-{
-    static_assert(lockstep_sources(true, 0) == 1, "the bisection searches one source at a time");
-    switch (p.nbuf == 2 ? p.nit : 0) {
-#define EMPP_NIT(N) \
-    case N: launch_one<false, false, 0, 1, N>(p, staged, lds, grid, stream); return;
-        EMPP_NIT(1) EMPP_NIT(2) EMPP_NIT(3) EMPP_NIT(4) EMPP_NIT(5) EMPP_NIT(6)
-        EMPP_NIT(7) EMPP_NIT(8) EMPP_NIT(9) EMPP_NIT(10) EMPP_NIT(11)
-#undef EMPP_NIT
-    default: launch_one<false, false, 0, 1, -1>(p, staged, lds, grid, stream);
-    }
-}
-
-// Guided fields launches over double-buffered tiles take the kernel with
-// the buffer count fixed at compile time.
-template <bool K, bool C, int G, int S>
-void launch_tiles(const PairParams &p, int staged, size_t lds, dim3 grid, hipStream_t stream)
-{
-    if constexpr (!K && !C && G >= 1) {
-        if (p.nbuf == 2) {
-            launch_one<K, C, G, S, 0>(p, staged, lds, grid, stream);
-            return;
-        }
-    }
-    launch_one<K, C, G, S>(p, staged, lds, grid, stream);
+    const size_t lds = pair_lds_bytes(p.D);
+    (void)hipFuncSetAttribute((const void *)pair_mixed_kernel<K, C, G, DB>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipLaunchKernelGGL((pair_mixed_kernel<K, C, G, DB>), grid, dim3(kBlockFp64), lds, stream, p);
 }
 
 template <bool K, bool C, int G>
-void launch_mode(const PairParams &p, int staged, size_t lds, dim3 grid, hipStream_t stream)
+void launch_mode(const PairParams &p, dim3 grid, hipStream_t stream)
 {
-    if constexpr (lockstep_sources(true, G) == 2) {
-        if (staged >= 2) {
-            launch_tiles<K, C, G, 2>(p, staged, lds, grid, stream);
-            return;
-        }
-    }
-    launch_tiles<K, C, G, 1>(p, staged, lds, grid, stream);
+    if (pair_two_buffers(p.D))
+        launch_kernel<K, C, G, true>(p, grid, stream);
+    else
+        launch_kernel<K, C, G, false>(p, grid, stream);
 }
 
 }  // namespace
 
-hipError_t launch_pair_mixed(const PairParams &p0, hipStream_t stream, bool kstar, bool count)
+hipError_t launch_pair_mixed(const PairParams &p, hipStream_t stream, bool kstar, bool count)
 {
-    PairParams p = p0;
-    if (p.guess > 3 || p.ad || p.recon == 1)
-        return hipErrorInvalidValue;  // fixed step, no warm start, linear reconstruction
-    const int staged = pair_staged_tile(p.D);
-    p.nbuf = pair_nbuf(p.D, staged);
+    // fixed step, no warm start, linear reconstruction, one wavefront per target
+    if (p.guess > 3 || p.ad || p.recon == 1 || p.sg_log2 != 0)
+        return hipErrorInvalidValue;
     const int64_t nblocks = (p.m + kBlockFp64 - 1) / kBlockFp64 * p.nsplit;
     if (nblocks < 1 || nblocks > INT32_MAX)
         return hipErrorInvalidConfiguration;
     dim3 grid((unsigned)nblocks);
-    const size_t lds = pair_lds_bytes(p.D, staged);
 #define EMPP_BY_GUESS(K, C)                                                                                  \
     do {                                                                                                    \
-        if (p.guess == 3) launch_mode<K, C, 3>(p, staged, lds, grid, stream);                                \
-        else if (p.guess == 2) launch_mode<K, C, 2>(p, staged, lds, grid, stream);                           \
-        else if (p.guess == 1) launch_mode<K, C, 1>(p, staged, lds, grid, stream);                           \
-        else launch_mode<K, C, 0>(p, staged, lds, grid, stream);                                             \
+        if (p.guess == 3) launch_mode<K, C, 3>(p, grid, stream);                                             \
+        else if (p.guess == 2) launch_mode<K, C, 2>(p, grid, stream);                                        \
+        else if (p.guess == 1) launch_mode<K, C, 1>(p, grid, stream);                                        \
+        else launch_mode<K, C, 0>(p, grid, stream);                                                          \
     } while (0)
-    if (!kstar && !count && p.guess == 0) {
-        launch_plain(p, staged, lds, grid, stream);
-    } else if (kstar) {
+    if (kstar) {
         if (count) EMPP_BY_GUESS(true, true); else EMPP_BY_GUESS(true, false);
     } else {
         if (count) EMPP_BY_GUESS(false, true); else EMPP_BY_GUESS(false, false);

@@ -7,32 +7,22 @@
 
 namespace empp {
 
-// Light-cone records of every (source j, slot b) at the present time T[head]
-// (b = 0 the newest slot): rec[j D + b] = {-2 D, L^2 - |D|^2} with
-// D = w_n - w_b and L = c (T[head] - T_b), the per-sample part of the split
-// sign test (lightcone_record).  Written once per pair pass, so that the
-// pair kernels' target blocks stage them instead of each recomputing them.
-__global__ void lightcone_records_kernel(const double4 *ring_w, const double *T, int64_t N, int D, int head,
-                                         double4 *rec)
+// Segment records of every (source, slot) from the velocity ring (a ring
+// read from a checkpoint; the newest slot has no segment).
+__global__ void segments_kernel(const double4 *ring_v, int64_t N, int D, double4 *seg)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N * (int64_t)D)
         return;
     const int64_t j = q / D;
-    const int b = (int)(q - j * D);
-    int ph = head - b;
-    ph += ph < 0 ? D : 0;
-    const double L = kC_LIGHT * (T[head] - T[ph]);
-    const double4 wn = ring_w[j * D + head];
-    rec[q] = lightcone_record(make_double4(wn.x, wn.y, wn.z, 0.0), ring_w[j * D + ph], L);
+    const int ph = (int)(q - j * D);
+    seg[q] = segment_record(ring_v[q], ring_v[j * D + (ph + 1 == D ? 0 : ph + 1)]);
 }
 
-hipError_t launch_lightcone_records(const double4 *ring_w, const double *T, int64_t N, int D, int head,
-                                    double4 *rec, hipStream_t s)
+hipError_t launch_segments(const double4 *ring_v, int64_t N, int D, double4 *seg, hipStream_t s)
 {
     const int64_t n = N * (int64_t)D;
-    hipLaunchKernelGGL(lightcone_records_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ring_w, T, N, D,
-                       head, rec);
+    hipLaunchKernelGGL(segments_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ring_v, N, D, seg);
     return hipGetLastError();
 }
 
@@ -162,6 +152,12 @@ __device__ inline void push_particle(const PushParams &p, int64_t i, double Ex, 
     double4 vn = make_double4(ux * ig, uy * ig, uz * ig, 1.0 / (p.t_next - p.t_now));
     p.ring_v[i * D + p.head] = vn;
     int nh = p.head + 1 == D ? 0 : p.head + 1;
+    // the segment that ends at this slot has its final velocity; the one
+    // that starts here has no acceleration before the next push
+    const int ph = p.head == 0 ? D - 1 : p.head - 1;
+    if (ph != nh)
+        p.seg[i * D + ph] = segment_record(p.ring_v[i * D + ph], vn);
+    p.seg[i * D + p.head] = p.seg[i * D + nh] = segment_record(vn, vn);
     p.ring_w[i * D + nh] = make_double4(y.x + vn.x * p.dt, y.y + vn.y * p.dt, y.z + vn.z * p.dt, 0.0);
     vn.w = 0.0;
     p.ring_v[i * D + nh] = vn;
@@ -217,7 +213,7 @@ __global__ __launch_bounds__(64 * SL) void merge_push_kernel(PushParams p)
 
 // Straight-line prior history: logical slot k = -(D-1)..0 (physical
 // index k + D - 1) at T_k = t0 + k dt, w_k = r + v0 (k dt), v_k = v0.
-__global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double *T, const double *r,
+__global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double4 *seg, double *T, const double *r,
                                      const double *u, int64_t N, int D, double t0, double dt)
 {
     // Rounded exactly as a plain IEEE evaluation (no fused multiply-add),
@@ -236,7 +232,9 @@ __global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double *T
     double kdt = (double)k * dt;
     ring_w[idx] = make_double4(r[i] + vx * kdt, r[N + i] + vy * kdt, r[2 * N + i] + vz * kdt, 0.0);
     double inv_h = s + 1 < D ? 1.0 / ((t0 + (double)(k + 1) * dt) - (t0 + kdt)) : 0.0;
-    ring_v[idx] = make_double4(vx, vy, vz, inv_h);
+    const double4 vr = make_double4(vx, vy, vz, inv_h);
+    ring_v[idx] = vr;
+    seg[idx] = segment_record(vr, vr);
     if (i == 0)
         T[s] = t0 + kdt;
 }
@@ -244,7 +242,7 @@ __global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double *T
 // [ns][3][N] component-major history (oldest first) -> ring layout with
 // logical slot s at physical slot s (head = D - 1).
 __global__ void history_to_ring_kernel(const double *w, const double *v, const double *T, double4 *ring_w,
-                                       double4 *ring_v, int64_t N, int D)
+                                       double4 *ring_v, double4 *seg, int64_t N, int D)
 {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= N * D)
@@ -255,7 +253,10 @@ __global__ void history_to_ring_kernel(const double *w, const double *v, const d
     const double *vs = v + s * 3 * N;
     ring_w[idx] = make_double4(ws[i], ws[N + i], ws[2 * N + i], 0.0);
     double inv_h = s + 1 < D ? 1.0 / (T[s + 1] - T[s]) : 0.0;
-    ring_v[idx] = make_double4(vs[i], vs[N + i], vs[2 * N + i], inv_h);
+    const double4 v1 = make_double4(vs[i], vs[N + i], vs[2 * N + i], inv_h);
+    const double *v2 = s + 1 < D ? vs + 3 * N : vs;
+    ring_v[idx] = v1;
+    seg[idx] = segment_record(v1, make_double4(v2[i], v2[N + i], v2[2 * N + i], 0.0));
 }
 
 // Ring -> [D][3][N] oldest first (logical order).
@@ -470,21 +471,21 @@ hipError_t launch_push(const PushParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_init_straight(double4 *rw, double4 *rv, double *T, const double *r, const double *u, int64_t N,
+hipError_t launch_init_straight(double4 *rw, double4 *rv, double4 *seg, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s)
 {
     int64_t tot = N * D;
-    hipLaunchKernelGGL(init_straight_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, rv, T, r, u,
+    hipLaunchKernelGGL(init_straight_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, rv, seg, T, r, u,
                        N, D, t0, dt);
     return hipGetLastError();
 }
 
 hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, double4 *rv,
-                                  int64_t N, int D, hipStream_t s)
+                                  double4 *seg, int64_t N, int D, hipStream_t s)
 {
     int64_t tot = N * D;
     hipLaunchKernelGGL(history_to_ring_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, w, v, T, rw,
-                       rv, N, D);
+                       rv, seg, N, D);
     return hipGetLastError();
 }
 
