@@ -22,14 +22,18 @@ namespace empp {
 int pair_fp64_tile(int D);
 hipError_t launch_pair_fp64(const PairParams &p, hipStream_t stream, bool kstar, bool count);
 hipError_t launch_pair_mixed(const PairParams &p, hipStream_t stream, bool kstar, bool count);
-hipError_t launch_segments(const double4 *ring_v, int64_t N, int D, double4 *seg, hipStream_t s);
+hipError_t launch_vel_pack(VelRing vel, int64_t q0, int64_t n, double4 *rec, hipStream_t s);
+hipError_t launch_vel_unpack(const double4 *rec, int64_t q0, int64_t n, VelRing vel, hipStream_t s);
+hipError_t launch_vel_accel(VelRing vel, int64_t N, int D, hipStream_t s);
+hipError_t launch_guess_lines(const double4 *ring_w, VelRing vel, const double *T, int64_t N, int D, int head, double dt,
+                              GuessLine *lines, hipStream_t s);
 hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, hipStream_t s);
 hipError_t launch_push(const PushParams &p, hipStream_t s);
-hipError_t launch_init_straight(double4 *rw, double4 *rv, double4 *seg, double *T, const double *r, const double *u, int64_t N,
+hipError_t launch_init_straight(double4 *rw, VelRing vel, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s);
-hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, double4 *rv,
-                                  double4 *seg, int64_t N, int D, hipStream_t s);
-hipError_t launch_ring_to_history(const double4 *rw, const double4 *rv, double *w, double *v, int64_t N, int D,
+hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, VelRing vel,
+                                  int64_t N, int D, hipStream_t s);
+hipError_t launch_ring_to_history(const double4 *rw, VelRing vel, double *w, double *v, int64_t N, int D,
                                   int head, hipStream_t s);
 hipError_t launch_newest_positions(const double4 *rw, double *r, int64_t N, int D, int head, hipStream_t s);
 hipError_t launch_diag(const double4 *rw, const double *u, int64_t N, int D, int head, double *out, hipStream_t s);
@@ -86,7 +90,7 @@ constexpr uint64_t kAlign = 256;
 uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    uint64_t ring_w, ring_v, seg, T, u, E, B, part, err, counters, diag, order, pos, skey, st, ad, kc, kc_bytes, total;
+    uint64_t ring_w, vel, lines, T, u, E, B, part, err, counters, diag, order, pos, skey, st, ad, kc, kc_bytes, total;
 };
 
 
@@ -160,9 +164,8 @@ Layout layout_for(const empp_config &c)
         return at;
     };
     L.ring_w = take(N * D * sizeof(double4));
-    L.ring_v = take(N * D * sizeof(double4));
-    // segment records (acceleration, c^2 - v^2) of every slot
-    L.seg = take(N * D * sizeof(double4));
+    L.vel = take(N * D * 4 * sizeof(double2));
+    L.lines = take(2 * N * sizeof(GuessLine));
     L.T = take(D * sizeof(double));
     L.u = take(3 * N * sizeof(double));
     L.E = take(3 * N * sizeof(double));
@@ -285,8 +288,8 @@ struct empp_ctx {
     template <typename Tp>
     Tp *at(uint64_t off) const { return reinterpret_cast<Tp *>(ws + off); }
     double4 *ring_w() const { return at<double4>(L.ring_w); }
-    double4 *ring_v() const { return at<double4>(L.ring_v); }
-    double4 *seg() const { return at<double4>(L.seg); }
+    VelRing vel() const { return VelRing{at<double2>(L.vel), cfg.n * (int64_t)cfg.depth}; }
+    GuessLine *lines() const { return at<GuessLine>(L.lines); }
     double *T() const { return at<double>(L.T); }
     double *u() const { return at<double>(L.u); }
     double *E() const { return at<double>(L.E); }
@@ -355,8 +358,8 @@ PairParams pair_params(empp_ctx *ctx)
 {
     PairParams p{};
     p.ring_w = ctx->ring_w();
-    p.ring_v = ctx->ring_v();
-    p.seg = ctx->seg();
+    p.vel = ctx->vel();
+    p.line = nullptr;
     p.T = ctx->T();
     p.n_src = ctx->cfg.n;
     p.D = ctx->cfg.depth;
@@ -431,7 +434,7 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
                 return e;
             GuessParams gp{};
             gp.ring_w = ctx->ring_w();
-            gp.ring_v = ctx->ring_v();
+            gp.vel = ctx->vel();
             gp.T = ctx->T();
             gp.centroid = cent_pair;
             gp.N = ctx->cfg.n;
@@ -465,7 +468,7 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
             return e;
         GuessParams gp{};
         gp.ring_w = ctx->ring_w();
-        gp.ring_v = ctx->ring_v();
+        gp.vel = ctx->vel();
         gp.T = ctx->T();
         gp.centroid = cent;
         gp.N = ctx->cfg.n;
@@ -481,9 +484,18 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
     });
 }
 
+// The guess data the launch's search mode starts from: the chord's for a
+// bisection (a cold warm start's too), else the newest velocity's.
+void set_guess_line(empp_ctx *ctx, PairParams &p)
+{
+    const bool chord = p.guess == EMPP_GUESS_BISECT || p.recon == 1 || (p.guess == EMPP_GUESS_PREVIOUS && p.kc_cold);
+    p.line = reinterpret_cast<const float4 *>(ctx->lines() + (chord ? 0 : ctx->cfg.n));
+}
+
 hipError_t launch_pair(empp_ctx *ctx, PairParams &p, bool kstar, float *G_pair = nullptr,
                        double3 *cent_pair = nullptr)
 {
+    set_guess_line(ctx, p);
     hipError_t eg = launch_guesses(ctx, p, G_pair, cent_pair);
     if (eg != hipSuccess)
         return eg;
@@ -625,8 +637,9 @@ empp_status empp_init_history_straight(empp_ctx *ctx)
     double *r_dev = ctx->part();
     HIP_TRY(hipMemcpyAsync(r_dev, ctx->r0.data(), 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipMemcpyAsync(ctx->u(), ctx->u0.data(), 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(launch_init_straight(ctx->ring_w(), ctx->ring_v(), ctx->seg(), ctx->T(), r_dev, ctx->u(), N, D, ctx->t_origin,
+    HIP_TRY(launch_init_straight(ctx->ring_w(), ctx->vel(), ctx->T(), r_dev, ctx->u(), N, D, ctx->t_origin,
                                  ctx->cfg.dt, ctx->stream));
+    HIP_TRY(launch_guess_lines(ctx->ring_w(), ctx->vel(), ctx->T(), N, D, D - 1, ctx->cfg.dt, ctx->lines(), ctx->stream));
     std::vector<int32_t> ord = morton_order(ctx->r0.data(), N);
     HIP_TRY(hipMemcpyAsync(ctx->order(), ord.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipMemsetAsync(ctx->E(), 0, 3 * N * sizeof(double), ctx->stream));
@@ -678,8 +691,9 @@ empp_status empp_set_history(empp_ctx *ctx, int32_t nslots, const double *T, con
         HIP_TRY(hipMemcpyAsync(tmp, w, tot * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(hipMemcpyAsync(tmp + tot, v, tot * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         HIP_TRY(hipMemcpyAsync(ctx->T(), T, D * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-        HIP_TRY(launch_history_to_ring(tmp, tmp + tot, ctx->T(), ctx->ring_w(), ctx->ring_v(), ctx->seg(), N, D,
+        HIP_TRY(launch_history_to_ring(tmp, tmp + tot, ctx->T(), ctx->ring_w(), ctx->vel(), N, D,
                                        ctx->stream));
+        HIP_TRY(launch_guess_lines(ctx->ring_w(), ctx->vel(), ctx->T(), N, D, D - 1, ctx->cfg.dt, ctx->lines(), ctx->stream));
         HIP_TRY(hipMemcpyAsync(ctx->u(), u, 3 * N * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         std::vector<int32_t> ord = morton_order(w + (uint64_t)(D - 1) * 3 * N, N);
         HIP_TRY(hipMemcpyAsync(ctx->order(), ord.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, ctx->stream));
@@ -747,8 +761,9 @@ empp_status empp_step(empp_ctx *ctx, int64_t nsteps)
         ctx->kc_valid = p.kc != nullptr;
         PushParams q{};
         q.ring_w = ctx->ring_w();
-        q.ring_v = ctx->ring_v();
-        q.seg = ctx->seg();
+        q.vel = ctx->vel();
+        q.lines = ctx->lines();
+        q.dt_cfg = ctx->cfg.dt;
         q.T = ctx->T();
         q.u = ctx->u();
         q.E = ctx->E();
@@ -915,6 +930,7 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
     p.kstar = kstar_dev;
     p.part = reinterpret_cast<double *>(ctx->scratch);
     // launched directly: no timing events, no guess buffers
+    set_guess_line(ctx, p);
     hipError_t e = ctx->cfg.precision == EMPP_MIXED
                        ? launch_pair_mixed(p, ctx->stream, kstar_dev != nullptr, ctx->counting)
                        : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
@@ -1040,7 +1056,7 @@ empp_status empp_get_history(empp_ctx *ctx, double *T, double *w, double *v)
     const uint64_t tot = 3 * (uint64_t)N * D;
     double *tmp = nullptr;
     HIP_TRY(hipMalloc((void **)&tmp, 2 * tot * sizeof(double)));
-    hipError_t e = launch_ring_to_history(ctx->ring_w(), ctx->ring_v(), tmp, tmp + tot, N, D, ctx->head, ctx->stream);
+    hipError_t e = launch_ring_to_history(ctx->ring_w(), ctx->vel(), tmp, tmp + tot, N, D, ctx->head, ctx->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(w, tmp, tot * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess)
@@ -1275,7 +1291,7 @@ static SampleParams sample_params(empp_ctx *ctx, uint64_t seed)
 {
     SampleParams sp{};
     sp.ring_w = ctx->ring_w();
-    sp.ring_v = ctx->ring_v();
+    sp.vel = ctx->vel();
     sp.T = ctx->T();
     sp.N = ctx->cfg.n;
     sp.D = ctx->cfg.depth;
@@ -1651,6 +1667,26 @@ empp_status file_to_dev(empp_ctx *ctx, FILE *f, void *dev, uint64_t bytes)
     return EMPP_OK;
 }
 
+// The velocity ring as records {v, 1/h}, through the partials' memory (no
+// launch is using it: the stream is drained around a checkpoint).
+empp_status vel_file(empp_ctx *ctx, FILE *f, bool save)
+{
+    const int64_t total = ctx->cfg.n * (int64_t)ctx->cfg.depth;
+    const int64_t room = (int64_t)(12 * sizeof(double) / sizeof(double4)) * ctx->nsplit * ctx->cfg.n;
+    double4 *rec = reinterpret_cast<double4 *>(ctx->part());
+    for (int64_t q0 = 0; q0 < total; q0 += room) {
+        const int64_t n = std::min(room, total - q0);
+        if (save)
+            HIP_TRY(launch_vel_pack(ctx->vel(), q0, n, rec, ctx->stream));
+        empp_status st = save ? dev_to_file(ctx, f, rec, n * sizeof(double4)) : file_to_dev(ctx, f, rec, n * sizeof(double4));
+        if (st != EMPP_OK)
+            return st;
+        if (!save)
+            HIP_TRY(launch_vel_unpack(rec, q0, n, ctx->vel(), ctx->stream));
+    }
+    return EMPP_OK;
+}
+
 // The target order indexes the history ring in the pair kernel: accept it
 // only as a permutation of 0..N-1.
 empp_status order_from_file(empp_ctx *ctx, FILE *f)
@@ -1710,7 +1746,7 @@ empp_status empp_save(empp_ctx *ctx, const char *path)
     if (st == EMPP_OK && h.stage == 1) {
         st = dev_to_file(ctx, f, ctx->ring_w(), (uint64_t)N * D * sizeof(double4));
         if (st == EMPP_OK)
-            st = dev_to_file(ctx, f, ctx->ring_v(), (uint64_t)N * D * sizeof(double4));
+            st = vel_file(ctx, f, true);
     }
     if (st == EMPP_OK && h.stage == 2) {
         st = dev_to_file(ctx, f, ctx->pos(), N * sizeof(double4));
@@ -1753,11 +1789,14 @@ empp_status empp_load(empp_ctx *ctx, const char *path)
     if (st == EMPP_OK && h.stage == 1) {
         st = file_to_dev(ctx, f, ctx->ring_w(), (uint64_t)N * D * sizeof(double4));
         if (st == EMPP_OK)
-            st = file_to_dev(ctx, f, ctx->ring_v(), (uint64_t)N * D * sizeof(double4));
+            st = vel_file(ctx, f, false);
         if (st == EMPP_OK) {
-            hipError_t e = launch_segments(ctx->ring_v(), N, D, ctx->seg(), ctx->stream);
+            hipError_t e = launch_vel_accel(ctx->vel(), N, D, ctx->stream);
+            if (e == hipSuccess)
+                e = launch_guess_lines(ctx->ring_w(), ctx->vel(), ctx->T(), N, D, h.head, ctx->cfg.dt, ctx->lines(),
+                                       ctx->stream);
             if (e != hipSuccess)
-                st = fail(EMPP_EDEVICE, "segment records: %s", hipGetErrorString(e));
+                st = fail(EMPP_EDEVICE, "derived history data: %s", hipGetErrorString(e));
         }
     }
     if (st == EMPP_OK && h.stage == 2) {

@@ -29,19 +29,87 @@ constexpr int kMaxSplits = 1024;   // source chunks of one launch
 
 // History layout in HBM (library-owned workspace):
 //   ring_w[j * D + p] = {x, y, z, 0}     position of source j at physical slot p
-//   ring_v[j * D + p] = {vx, vy, vz, 1/h} velocity leaving that slot and the
-//                                         inverse length of its segment (0: newest)
-//   seg[j * D + p]    = {ax, ay, az, C2}  acceleration (v_{p+1} - v_p)/h of the
-//                                         segment that starts there and c^2 - |v_p|^2
+//   vel: four planes of N D 16-byte records, record j * D + p of each
+//     {vx, vy}, {vz, ax}, {ay, az}, {1/h, vz} velocity leaving that slot, the
+//                                         acceleration (v_{p+1} - v_p)/h of the
+//                                         segment that starts there and its
+//                                         inverse length (0: newest)
 //   T[p]                                  slot time
 // Slot p holds logical slot "back" b (0 = newest) when p = (head - b) mod D.
-// A source's whole history is one contiguous 32*D-byte block, so a block
-// of targets stages it into LDS with straight coalesced loads.
+// A source's positions are one contiguous 32*D-byte block, so a block
+// of targets stages them into LDS with straight coalesced loads.
+
+// The velocity ring in planes.  The pair kernels gather a lane's bracket
+// record from L2 through the vector L1, which takes 37 cycles for a
+// wavefront's 16-byte (or 8-byte) load from random places in 8 KiB, 25 in
+// 2 KiB, 16.5 contiguous: three loads from dense planes instead of four from
+// two 32-byte records (N = 65536, D = 512: 26.3 -> 25.7 ms, warm start 30.9 ->
+// 28.3; mixed precision, which also takes the next slot's velocity and the
+// inverse length, four loads as before).
+struct VelRing {
+    double2 *plane;  // plane k at plane + k n
+    int64_t n;
+    __device__ double3 v(int64_t q) const
+    {
+        const double2 a = plane[q];
+        return make_double3(a.x, a.y, plane[n + q].x);
+    }
+    __device__ double inv_h(int64_t q) const { return plane[3 * n + q].x; }
+    __device__ void set_v(int64_t q, double3 v, double ih) const
+    {
+        plane[q] = make_double2(v.x, v.y);
+        plane[n + q].x = v.z;
+        plane[3 * n + q] = make_double2(ih, v.z);
+    }
+    // acceleration of the segment at q that ends with velocity v2
+    __device__ void set_a(int64_t q, double3 v1, double3 v2, double ih) const
+    {
+        plane[n + q].y = (v2.x - v1.x) * ih;
+        plane[2 * n + q] = make_double2((v2.y - v1.y) * ih, (v2.z - v1.z) * ih);
+    }
+};
+
+// Data of a source for the guessed bracket, in float: the slot
+// b = d0.l + sqrt((d0.l)^2 + k |d0|^2), d0 = r - w_n the target's offset from
+// the newest sample; {w_n - ref, k}, {l, -} with ref the sample of particle 0
+// before the newest.  lines[2 j] from the chord, lines[2 (N + j)] from the
+// newest velocity; made by the push for the next pass (and when a history is
+// set): made in the pair kernel, one wavefront's work per tile, the pass took
+// 23.9 ms instead of 23.6 at N = 65536, D = 512, and 29.1 instead of 28.4 at
+// D = 1024.
+struct GuessLine {
+    float4 a, b;
+};
+
+// Along the chord from the newest to the oldest sample wo, Lo = c (t - T)
+// there, the sign-test value is alpha b^2 - 2 alpha b (d0.l) - |d0|^2, exactly
+// so on a straight path: alpha = (Lo^2 - |D|^2) / (D - 1)^2, l = D / ((D - 1)
+// alpha), k = 1 / alpha.
+__device__ inline GuessLine chord_line(double3 wn, double3 wo, double Lo, int depth, double3 ref)
+{
+    const double dx = wn.x - wo.x, dy = wn.y - wo.y, dz = wn.z - wo.z, n = (double)(depth - 1);
+    const double ia = n * n / (Lo * Lo - (dx * dx + dy * dy + dz * dz));
+    const double f = ia / n;
+    return GuessLine{make_float4((float)(wn.x - ref.x), (float)(wn.y - ref.y), (float)(wn.z - ref.z), (float)ia),
+                     make_float4((float)(dx * f), (float)(dy * f), (float)(dz * f), 0.0f)};
+}
+
+// Straight-line look-back: with beta the newest velocity / c, the positive
+// root of (1 - beta^2) s^2 - 2 (R.beta) s - R^2 = 0, in steps of c dt.
+__device__ inline GuessLine straight_line(double3 wn, double3 vn, double dt, double3 ref)
+{
+    const double ic = 1.0 / kC_LIGHT;
+    const double bx = vn.x * ic, by = vn.y * ic, bz = vn.z * ic;
+    const double ig2 = 1.0 / (1.0 - (bx * bx + by * by + bz * bz));
+    const double is = 1.0 / (kC_LIGHT * dt), f = ig2 * is;
+    return GuessLine{make_float4((float)(wn.x - ref.x), (float)(wn.y - ref.y), (float)(wn.z - ref.z), (float)(f * is)),
+                     make_float4((float)(bx * f), (float)(by * f), (float)(bz * f), 0.0f)};
+}
 
 struct PairParams {
     const double4 *ring_w;
-    const double4 *ring_v;
-    const double4 *seg;
+    VelRing vel;
+    const float4 *line;  // guess data of the mode, [N][2]
     const double *T;
     int64_t n_src;      // sources N
     int32_t D;
@@ -91,8 +159,9 @@ constexpr uint16_t kBracketBefore = 0xFFFF;
 
 struct PushParams {
     double4 *ring_w;
-    double4 *ring_v;
-    double4 *seg;
+    VelRing vel;
+    GuessLine *lines;   // [2][N]
+    double dt_cfg;      // the configured step (straight-line guesses)
     double *T;
     double *u;          // [3][N]
     double *E;          // [3][N] self-field of the step (written by the merge)
@@ -171,14 +240,6 @@ __device__ inline void report_error(unsigned long long *err, int64_t a, int64_t 
     unsigned long long key = ((unsigned long long)(uint32_t)a << 32) | (uint32_t)j;
     atomicMin(&err[0], key);
     atomicOr(&err[1], bit);
-}
-
-// Segment record of a slot from its velocity record and the next newer one's.
-__device__ inline double4 segment_record(double4 v1, double4 v2)
-{
-    const double c2 = kC_LIGHT * kC_LIGHT;
-    const double C2 = __builtin_fma(-v1.x, v1.x, __builtin_fma(-v1.y, v1.y, __builtin_fma(-v1.z, v1.z, c2)));
-    return make_double4((v2.x - v1.x) * v1.w, (v2.y - v1.y) * v1.w, (v2.z - v1.z) * v1.w, C2);
 }
 
 // Reciprocal of a positive normal double: hardware estimate plus one

@@ -706,7 +706,7 @@ __device__ void pair_features(const SampleParams &p, int64_t i, int64_t j, float
     const int h = p.head;
     double4 r = p.ring_w[i * D + h];
     double4 wn = p.ring_w[j * D + h];
-    double4 vn = p.ring_v[j * D + h];
+    double3 vn = p.vel.v(j * D + h);
     int h4 = h - 4;
     h4 += h4 < 0 ? D : 0;
     double4 w4 = p.ring_w[j * D + h4];
@@ -724,12 +724,12 @@ __device__ void pair_features(const SampleParams &p, int64_t i, int64_t j, float
     Xrow[8] = (float)((wn.z - w4.z) / span);
     Xrow[9] = 0.0f;  // log1p((t - T_n)/dt) with t = T_n
     // exact bracket (FP64 sign tests on the history in HBM) and root
-    const double R0sq = offset_sq(Rx, Ry, Rz);
     auto test = [&](int b) {
         int ph = h - b;
         ph += ph < 0 ? D : 0;
         const double L = c * (p.t - p.T[ph]);
-        return lightcone_positive(lightcone_record(wn, p.ring_w[j * D + ph], L), Rx, Ry, Rz, R0sq);
+        const double4 w = p.ring_w[j * D + ph];
+        return lightcone_value(make_double3(r.x - w.x, r.y - w.y, r.z - w.z), L * L) > 0.0;
     };
     int probes = 0;
     int b = search_bisect(test, D, probes);
@@ -738,7 +738,7 @@ __device__ void pair_features(const SampleParams &p, int64_t i, int64_t j, float
     int ph1 = h - bb;
     ph1 += ph1 < 0 ? D : 0;
     double4 w1 = p.ring_w[j * D + ph1];
-    double4 v1 = p.ring_v[j * D + ph1];
+    double3 v1 = p.vel.v(j * D + ph1);
     double L1 = c * (p.t - p.T[ph1]);
     double dx = r.x - w1.x, dy = r.y - w1.y, dz = r.z - w1.z;
     double C2 = c * c - (v1.x * v1.x + v1.y * v1.y + v1.z * v1.z);
@@ -814,7 +814,7 @@ __global__ __launch_bounds__(256) void mlp_group_guess_kernel(const MlpPacked *n
                 int64_t j = row / p.ngroups, grp = row - j * p.ngroups;
                 double3 cen = p.centroid[grp];
                 double4 wn = p.ring_w[j * D + h];
-                double4 vn = p.ring_v[j * D + h];
+                double3 vn = p.vel.v(j * D + h);
                 double4 w4 = p.ring_w[j * D + h4];
                 f[0] = (float)((cen.x - wn.x) * p.inv_sigma);
                 f[1] = (float)((cen.y - wn.y) * p.inv_sigma);

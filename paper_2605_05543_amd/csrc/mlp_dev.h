@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "empp_dev.h"
+
 namespace empp {
 
 constexpr int kIn = 10;
@@ -81,7 +83,7 @@ struct TrainRun {
 
 struct SampleParams {
     const double4 *ring_w;
-    const double4 *ring_v;
+    VelRing vel;
     const double *T;
     int64_t N;
     int32_t D;
@@ -93,7 +95,7 @@ struct SampleParams {
 
 struct GuessParams {
     const double4 *ring_w;
-    const double4 *ring_v;
+    VelRing vel;
     const double *T;
     const double3 *centroid;  // [ngroups]
     int64_t N;

@@ -3,9 +3,8 @@
 //
 // One thread owns one target.  A block of kBlockFp64 (1024) threads walks its
 // chunk of sources in staged tiles of up to 16 sources: the tile's
-// histories, as the per-sample part of the split light-cone test (offsets
-// from each source's newest sample and L^2 - |offset|^2, see pair_common.h),
-// are staged once into LDS, double-buffered behind one barrier per tile, and
+// positions, with the square of each slot's light distance, are staged once
+// into LDS, double-buffered behind one barrier per tile, and
 // every target of the block then searches them, so each history byte read
 // from L2/HBM serves 1024 targets.  Source by source, a guessed bracket is
 // confirmed by the two samples that define it, the two velocity records are
@@ -23,15 +22,21 @@
 // modes.  MIX selects the mixed-precision field evaluation (root,
 // reconstruction and LW terms in FP32 around FP64 coefficients).
 //
-// What bounds it: the latency of a pair's chain (LDS reads of the confirming
-// samples, a gather of two 32-byte records from L2, about 70 dependent FP64
-// instructions) on four wavefronts per SIMD, then vector issue.  The history
-// is searched by guess and confirmation in every mode, the bisection's too:
-// the unrolled bisection's ten probes of 32 bytes kept the LDS busy for nine
-// tenths of the pass at N = 65536, D = 512 (33.1 ms; with a guess from the
-// oldest sample, the acceleration and c^2 - v^2 of each segment kept with the
-// history, and the root's square root reused as eta . v', 26.1 ms: 141 vector
-// instructions per wavefront and pair against 193).
+// What bounds it: vector issue (137 instructions per wavefront and pair at
+// N = 65536, D = 512, the VALU busy 69 % of the time), the vector L1 (three
+// 16-byte gathers of a lane's segment and the tile's loads) and the latency
+// of a pair's chain (LDS reads of the confirming samples, the gather from L2,
+// about 70 dependent FP64 instructions) on four wavefronts per SIMD.
+// The history is searched by guess and confirmation in every mode, the
+// bisection's too: the unrolled bisection's ten probes of 32 bytes kept the
+// LDS busy for nine tenths of the pass (33.1 ms; guessed along the chord to
+// the oldest sample, with each segment's acceleration kept with the history
+// and the root's square root reused as eta . v', 26.1 ms).  Positions are
+// staged as they are and tested as L^2 - |r - w|^2, velocities gathered from
+// planes and the guess's data made by the push: 23.7 ms (26.1 before), warm
+// start 26.8 (30.8), mixed straight-line 25.9 (27.4), D = 1024 28.5 (31.0);
+// a curving history that bisects pays nine instructions a probe instead of
+// six (N = 16384: 2.63 ms, 2.55 before).
 #pragma once
 
 #include "pair_common.h"
@@ -66,15 +71,15 @@ constexpr size_t pair_lds_bytes(int D)
     const bool two = pair_two_buffers(D);
     const size_t ts = (size_t)pair_staged_tile(D);
     return (two ? 4 * (size_t)kHalfRecs : 2 * (size_t)D) * sizeof(double2) + (size_t)((D + 1) & ~1) * sizeof(double) +
-           (two ? (size_t)((D + 3) & ~3) * sizeof(uint32_t) : 0) + 2 * ts * sizeof(float4) +
-           2 * kWaves * ts * sizeof(float) + 3 * ts * 8 * sizeof(double);
+           (two ? (size_t)((D + 3) & ~3) * sizeof(uint32_t) : 0) + 2 * ts * 2 * sizeof(float4) +
+           2 * kWaves * ts * sizeof(float);
 }
 
 static_assert(pair_lds_bytes(kMaxDepth) <= 160 * 1024,
               "the deepest history's tile, light distances and per-source data fit a CU's LDS");
 static_assert(pair_lds_bytes(kHalfRecs) <= 160 * 1024, "the deepest double-buffered tiles fit with the slot table");
-// its 16-bit byte offsets of 32-byte ring entries
-static_assert((kHalfRecs - 1) * 32 < 65536, "slot table offsets fit 16 bits");
+// its 16-bit byte offsets of 16-byte ring entries
+static_assert((kHalfRecs - 1) * 16 < 65536, "slot table offsets fit 16 bits");
 
 namespace {
 
@@ -96,8 +101,8 @@ __device__ inline double sqrt_pos(double x)
 // linear, linear2, LW_E, LW_B) without the factor kq, which the sums take at
 // the end.  d = r - w_1, the target's offset from the bracket's older sample,
 // C0 = L1^2 - |d|^2 (the sign test's value there), L1 = c (t - t_1); v1 the
-// velocity, a the acceleration (zero out of history) and C2 = c^2 - |v1|^2
-// of the bracket's segment.  E, and h = eta_hat / c for B = h x E.  Returns
+// velocity and a the acceleration (zero out of history) of the bracket's
+// segment.  E, and h = eta_hat / c for B = h x E.  Returns
 // false on a numerical failure (negative discriminant, eta <= 0), which
 // reaches the last test as a NaN.
 // The root sq of the discriminant is eta . v' at v_1, C2 dt being
@@ -107,13 +112,14 @@ __device__ inline double sqrt_pos(double x)
 // MID and mid: Eq. (mid) with the bracket's other velocity v2 and dw =
 // w_2 - w_1 (the accuracy ablation).
 template <bool MID>
-__device__ __forceinline__ bool lw_pair(double3 d, double C0, double L1, double4 v1, double3 a, double C2, double3 &E,
-                                        double3 &h, double &en, double3 &vr, bool mid, double4 v2, double3 dw)
+__device__ __forceinline__ bool lw_pair(double3 d, double C0, double L1, double3 v1, double3 a, double3 &E, double3 &h,
+                                        double &en, double3 &vr, bool mid, double3 v2, double3 dw)
 {
     const double c = kC_LIGHT;
     const double c2 = c * c;
     // C2 dt^2 + 2 C1h dt + C0 = 0 (Eq. dt with C1 = 2 C1h); the physical
     // root -(C1h + sqrt(C1h^2 - C2 C0))/C2 in Vieta's form.
+    const double C2 = __builtin_fma(-v1.x, v1.x, __builtin_fma(-v1.y, v1.y, __builtin_fma(-v1.z, v1.z, c2)));
     const double C1h = __builtin_fma(d.x, v1.x, __builtin_fma(d.y, v1.y, __builtin_fma(d.z, v1.z, -c * L1)));
     const double disc = __builtin_fma(C1h, C1h, -(C2 * C0));
     const double sq = sqrt_pos(disc);
@@ -308,7 +314,6 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     double rx = 0, ry = 0, rz = 0;
     double3 vt = make_double3(0.0, 0.0, 0.0);  // target's present velocity (adaptive step)
     double eta_min = __longlong_as_double((long long)kPosInfBits), dv2_max = 0.0;
-    int64_t tgt = a;    // index the outputs are written at
     int32_t self = -1;  // source left out (sources number at most 2^31)
     if (active) {
         if (p.x) {
@@ -317,18 +322,21 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             rz = p.x[2 * p.m + a];
             self = p.self_index ? (int32_t)p.self_index[a] : -1;
         } else {
-            tgt = p.order ? (int64_t)p.order[a] : a;
+            const int64_t tgt = p.order ? (int64_t)p.order[a] : a;
             double4 w = p.ring_w[tgt * D + p.head];
             rx = w.x;
             ry = w.y;
             rz = w.z;
             self = (int32_t)tgt;
             if (ADAPT) {
-                double4 vn = p.ring_v[tgt * D + p.head];
-                vt = make_double3(vn.x, vn.y, vn.z);
+                vt = p.vel.v(tgt * D + p.head);
             }
         }
     }
+    // offset from the sample of particle 0 before the newest, in float, for
+    // the guesses (GuessLine)
+    const double4 ref = p.ring_w[p.head == 0 ? D - 1 : p.head - 1];
+    const float rfx = (float)(rx - ref.x), rfy = (float)(ry - ref.y), rfz = (float)(rz - ref.z);
     // field sums: FP64 with Neumaier compensation, or FP32 with two-sum
     using Real = std::conditional_t<MIX, float, double>;
     Real sum[6] = {0, 0, 0, 0, 0, 0}, comp[6] = {0, 0, 0, 0, 0, 0};
@@ -341,50 +349,39 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     const float inv_cdt = (float)(1.0 / (kC_LIGHT * p.dt));
     const int64_t grp_index = a >> p.g_shift;  // surrogate group of this target
 
-    // LDS: the tile buffers, then the light distance of every logical slot
-    // (shared by all sources).  A buffer holds its TS * D records
-    // {-2 D, A} of the split sign test (lightcone_record) as two arrays of
-    // 16-byte halves, {-2 D_x, -2 D_y} then {-2 D_z, A}, hrec halves apart:
-    // lanes that probe different slots then spread over twice as many LDS
-    // bank groups as with 32-byte records.  With two buffers the distance is
-    // the fixed kHalfRecs, so a probe's reads share one address (the others
-    // at immediate offsets).
+    // LDS: the tile buffers, then the light distance L(b) = c (t - T_b) of
+    // every logical slot (shared by all sources).  A buffer holds its TS * D
+    // records {x, y, z, L^2} as two arrays of 16-byte halves, {x, y} then
+    // {z, L^2}, hrec halves apart: lanes that probe different slots then
+    // spread over twice as many LDS bank groups as with 32-byte records.
+    // With two buffers the distance is the fixed kHalfRecs, so a probe's
+    // reads share one address (the others at immediate offsets).
     constexpr int nbuf = DB ? 2 : 1;
     const int TS = DB ? p.tile : 1;
     const int hrec = DB ? kHalfRecs : D;
     const uint32_t hbytes = DB ? (uint32_t)(kHalfRecs * sizeof(double2)) : (uint32_t)D * (uint32_t)sizeof(double2);
     double2 *const halves = reinterpret_cast<double2 *>(lds);
     double *Ls = reinterpret_cast<double *>(halves + nbuf * 2 * hrec);
-    // slot table (two buffers): for back offset b, the byte offset in a ring
+    // slot table (two buffers): for back offset b, the byte offset in a plane's
     // row of physical slot (head - b) mod D and, above 16 bits, of the next
     // newer slot's (the bracket's two velocity records)
     uint32_t *slot_off = reinterpret_cast<uint32_t *>(Ls + ((D + 1) & ~1));
-    float4 *line = reinterpret_cast<float4 *>(slot_off + (DB ? ((D + 3) & ~3) : 0));  // [buffer][source]
-    float *gcorr = reinterpret_cast<float *>(line + 2 * TS);  // [buffer][wavefront][source]
-    // Per-source data of three consecutive staged tiles (tile i in slot
-    // i % 3): the newest sample w_n and the vector the guess is made from
-    // (the oldest sample of a bisection, else the newest velocity).  Eight
-    // threads per source load a double each, two tiles ahead of the tile's
-    // search, and write it a tile later, so that no wavefront waits for it.
+    float4 *line = reinterpret_cast<float4 *>(slot_off + (DB ? ((D + 3) & ~3) : 0));  // [buffer][source][2]
+    float *gcorr = reinterpret_cast<float *>(line + 2 * TS * 2);  // [buffer][wavefront][source]
+    // The guess's data of a tile's sources and the surrogate's corrections
+    // (guess mode 1, for groups of 64 or more targets: whole wavefronts), one
+    // value a thread, are loaded ahead like its positions.
     constexpr bool kChord = GUESS == 0 || GUESS == 5;
-    constexpr bool kLine = GUESS <= 2 || GUESS == 5;
-    double *aux = reinterpret_cast<double *>(gcorr + 2 * kWaves * TS);
-    double aux_pf = 0.0;
-    const char *const aux_src = [&]() {
-        const int oldest = p.head + 1 == D ? 0 : p.head + 1;
-        const double4 *v = kChord ? p.ring_w + oldest : p.ring_v + p.head;
-        const double4 *at = ((tid & 4) ? v : p.ring_w + p.head) + (int64_t)(tid >> 3) * D;
-        return reinterpret_cast<const char *>(at) + (tid & 3) * sizeof(double);
-    }();
-    auto load_aux = [&](int64_t jt, int ns) {
+    float line_pf = 0.0f;
+    const int gc_w = tid / TS, gc_s = tid - gc_w * TS;
+    const int64_t gc_a = (int64_t)bxi * targets + (gc_w & ((1 << tw_log2) - 1)) * 64;
+    float gc_pf = 0.0f;
+    auto load_line = [&](int64_t jt, int ns) {
         if (tid < 8 * ns)
-            aux_pf = *reinterpret_cast<const double *>(aux_src + jt * D * (int64_t)sizeof(double4));
+            line_pf = reinterpret_cast<const float *>(p.line + 2 * jt)[tid];
+        if (GUESS == 1 && tid < kWaves * TS && gc_s < ns && gc_a < p.m)
+            gc_pf = p.G[(jt + gc_s) * p.g_groups + (gc_a >> p.g_shift)];
     };
-    auto put_aux = [&](int slot3, int ns) {
-        if (tid < 8 * ns)
-            aux[slot3 * TS * 8 + tid] = aux_pf;
-    };
-    auto next3 = [](int i) { return i == 2 ? 0 : i + 1; };
     // the present time is the newest slot's (the clock lives in T)
     const double tnow = p.T[p.head];
     for (int b = tid; b < D; b += kBlockFp64) {
@@ -393,16 +390,18 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
         Ls[b] = kC_LIGHT * (tnow - p.T[ph]);
         if constexpr (DB) {
             const int ph2 = ph + 1 == D ? 0 : ph + 1;  // back offset b - 1 (read for b >= 1)
-            slot_off[b] = (uint32_t)ph * (uint32_t)sizeof(double4) | (uint32_t)ph2 * (uint32_t)sizeof(double4) << 16;
+            slot_off[b] = (uint32_t)ph * (uint32_t)sizeof(double2) | (uint32_t)ph2 * (uint32_t)sizeof(double2) << 16;
         }
     }
-    // Record q of a tile: source q / D (q < TS D), slot q % D, computed from
-    // the position while staging.  A thread's records, q = tid + 1024 k, keep
-    // their source and slot in every tile, so a load is a uniform row base plus
-    // a fixed 32-bit offset.  Positions are prefetched into registers one tile
-    // ahead (the first two of each thread: a whole tile with two buffers), so
-    // the latency overlaps the previous tile's work; deeper histories load
-    // the rest in place.
+    // Record q of a tile: source q / D (q < TS D), slot q % D.  A thread's
+    // records, q = tid + 1024 k, keep their source and slot in every tile: a
+    // load is a uniform row base plus a fixed 32-bit offset.  Positions are
+    // prefetched into registers one tile ahead (the first two of each thread:
+    // a whole tile with two buffers), so the latency overlaps the previous
+    // tile's work; deeper histories load the rest in place.  Records {-2 D,
+    // L^2 - |D|^2} (D from the newest sample) save three instructions per
+    // probe but are computed here: 25.7 ms instead of 23.9 at N = 65536,
+    // D = 512, 30.4 instead of 29.1 at D = 1024.
     auto src_of = [&](int q) { return DB ? q / D : 0; };
     auto pos_off = [&](int q) {
         const int s = src_of(q);
@@ -412,88 +411,52 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     };
     const int qa = min(tid, TS * D - 1), qb = min(tid + kBlockFp64, TS * D - 1);
     const uint32_t off_a = pos_off(qa), off_b = pos_off(qb);
-    const int sa = src_of(qa), sb = src_of(qb);
-    auto fetch = [&](int64_t jt, int nrec, int q, uint32_t off, double4 &w) {
+    const int ba = qa - src_of(qa) * D, bb = qb - src_of(qb) * D;
+    auto fetch = [&](int64_t jt, int nrec, int q, uint32_t off, double3 &w) {
         if (q < nrec)
-            w = *reinterpret_cast<const double4 *>(reinterpret_cast<const char *>(p.ring_w + jt * D) + off);
+            w = *reinterpret_cast<const double3 *>(reinterpret_cast<const char *>(p.ring_w + jt * D) + off);
     };
-    auto put = [&](int bi, int slot3, int nrec, int q, int s, int b, const double4 &w) {
+    auto put = [&](int bi, int nrec, int q, const double3 &w, int b) {
         if (q < nrec) {
-            const double *wn = aux + (slot3 * TS + s) * 8;
-            const double4 r = lightcone_record(make_double4(wn[0], wn[1], wn[2], 0.0), w, Ls[b]);
+            const double L = Ls[b];
             double2 *xy = halves + bi * 2 * hrec + q;
-            xy[0] = make_double2(r.x, r.y);
-            xy[hrec] = make_double2(r.z, r.w);
+            xy[0] = make_double2(w.x, w.y);
+            xy[hrec] = make_double2(w.z, L * L);
         }
     };
     // Tile jt of ns sources into buffer bi, from the prefetched positions.
-    auto stage = [&](int bi, int slot3, int64_t jt, int ns, const double4 &w0, const double4 &w1) {
-        if (kLine && tid < ns) {
-            // the guessed slot b = d0.l + sqrt((d0.l)^2 + k |d0|^2) in float
-            const double *ax = aux + (slot3 * TS + tid) * 8;
-            if constexpr (kChord) {
-                // along the chord from the newest to the oldest sample the
-                // sign-test value is alpha b^2 - 2 alpha b (d0.l) - |d0|^2,
-                // exactly so on a straight path: alpha = (L^2 - |D|^2) /
-                // (D - 1)^2 of the oldest sample, l = D / ((D - 1) alpha)
-                const double dx = ax[0] - ax[4], dy = ax[1] - ax[5], dz = ax[2] - ax[6];
-                const double Lo = Ls[D - 1], n = (double)(D - 1);
-                const double ia = n * n / (Lo * Lo - (dx * dx + dy * dy + dz * dz));
-                const double f = ia / n;
-                line[bi * TS + tid] = make_float4((float)(dx * f), (float)(dy * f), (float)(dz * f), (float)ia);
-            } else {
-                // straight-line look-back: with beta the source's newest
-                // velocity / c, the positive root of
-                // (1 - beta^2) s^2 - 2 (R.beta) s - R^2 = 0, in steps of c dt
-                const double ic = 1.0 / kC_LIGHT;
-                const double bx = ax[4] * ic, by = ax[5] * ic, bz = ax[6] * ic;
-                const double ig2 = 1.0 / (1.0 - (bx * bx + by * by + bz * bz));
-                const double is = 1.0 / (kC_LIGHT * p.dt), f = ig2 * is;
-                line[bi * TS + tid] = make_float4((float)(bx * f), (float)(by * f), (float)(bz * f), (float)(f * is));
-            }
-        }
-        if (GUESS == 1 && tid < kWaves * TS) {
-            // guess mode 1: the surrogate's correction for groups of 64 or
-            // more targets (whole wavefronts) is staged with the tile
-            const int w = tid / TS, sj = tid - w * TS;
-            const int64_t aw = (int64_t)bxi * targets + (w & ((1 << tw_log2) - 1)) * 64;
-            if (sj < ns && aw < p.m)
-                gcorr[(bi * kWaves + w) * TS + sj] = p.G[(jt + sj) * p.g_groups + (aw >> p.g_shift)];
-        }
+    auto stage = [&](int bi, int64_t jt, int ns, const double3 &w0, const double3 &w1) {
+        if (tid < 8 * ns)
+            reinterpret_cast<float *>(line + bi * TS * 2)[tid] = line_pf;
+        if (GUESS == 1 && tid < kWaves * TS && gc_s < ns)
+            gcorr[(bi * kWaves + gc_w) * TS + gc_s] = gc_pf;
         const int nrec = ns * D;
-        put(bi, slot3, nrec, tid, sa, qa - sa * D, w0);
-        put(bi, slot3, nrec, tid + kBlockFp64, sb, qb - sb * D, w1);
+        put(bi, nrec, tid, w0, ba);
+        put(bi, nrec, tid + kBlockFp64, w1, bb);
         if constexpr (!DB)
             for (int q = tid + 2 * kBlockFp64; q < nrec; q += kBlockFp64) {
-                double4 w;
+                double3 w;
                 fetch(jt, nrec, q, pos_off(q), w);
-                put(bi, slot3, nrec, q, 0, q, w);
+                put(bi, nrec, q, w, q);
             }
     };
     auto tile_size = [&](int i) { return min(nj - i, TS); };
-    double4 pf0, pf1;
+    double3 pf0, pf1;
     auto prefetch = [&](int i) {
-        fetch(j0 + i, tile_size(i) * D, tid, off_a, pf0);
-        fetch(j0 + i, tile_size(i) * D, tid + kBlockFp64, off_b, pf1);
+        const int ns = tile_size(i);
+        fetch(j0 + i, ns * D, tid, off_a, pf0);
+        fetch(j0 + i, ns * D, tid + kBlockFp64, off_b, pf1);
+        load_line(j0 + i, ns);
     };
     // Two buffers: tile i + 1 is written while tile i is searched, and one
     // barrier per tile both publishes tile i + 1 and retires tile i's
     // buffer for tile i + 2.  One buffer (deep histories): stage, then
     // search, with a barrier on either side.
-    int cur3 = 0;  // the searched tile's slot of the per-source data
     if (nj > 0) {
         prefetch(0);
-        load_aux(j0, tile_size(0));
-        put_aux(0, tile_size(0));
-        if (TS < nj) {
-            load_aux(j0 + TS, tile_size(TS));
-            put_aux(1, tile_size(TS));
-        }
-        if (2 * TS < nj)
-            load_aux(j0 + 2 * TS, tile_size(2 * TS));
+        __syncthreads();  // light distances
         if (DB) {
-            __syncthreads();
-            stage(0, 0, j0, tile_size(0), pf0, pf1);
+            stage(0, j0, tile_size(0), pf0, pf1);
             if (TS < nj)
                 prefetch(TS);
             __syncthreads();
@@ -509,25 +472,16 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     for (int i0 = 0; i0 < nj; i0 += TS) {
         if (DB) {
             if (i0 + TS < nj) {
-                stage(cb ^ 1, next3(cur3), j0 + i0 + TS, tile_size(i0 + TS), pf0, pf1);
-                if (i0 + 2 * TS < nj) {
+                stage(cb ^ 1, j0 + i0 + TS, tile_size(i0 + TS), pf0, pf1);
+                if (i0 + 2 * TS < nj)
                     prefetch(i0 + 2 * TS);
-                    put_aux(next3(next3(cur3)), tile_size(i0 + 2 * TS));
-                    if (i0 + 3 * TS < nj)
-                        load_aux(j0 + i0 + 3 * TS, tile_size(i0 + 3 * TS));
-                }
             }
         } else {
             __syncthreads();
-            stage(0, cur3, j0 + i0, tile_size(i0), pf0, pf1);
+            stage(0, j0 + i0, tile_size(i0), pf0, pf1);
             __syncthreads();
             if (i0 + TS < nj)
                 prefetch(i0 + TS);
-            if (i0 + 2 * TS < nj) {
-                put_aux(next3(next3(cur3)), tile_size(i0 + 2 * TS));
-                if (i0 + 3 * TS < nj)
-                    load_aux(j0 + i0 + 3 * TS, tile_size(i0 + 3 * TS));
-            }
         }
         const int ns = tile_size(i0);
         for (int s = sg; s < ns; s += SG) {
@@ -537,48 +491,55 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             if (GUESS == 4)
                 load_bracket(s + SG < ns ? i0 + s + SG : i0 + TS + sg);
             if (active) {
-                // the target's offset d0 = r - w_n from the source's newest
-                // sample, and |d0|^2 (the pair's part of the sign test)
-                const double *wn = aux + (cur3 * TS + s) * 8;
-                const double d0x = rx - wn[0], d0y = ry - wn[1], d0z = rz - wn[2];
-                const double R0 = offset_sq(d0x, d0y, d0z);
-                // a target on the source's present position has eta = 0 (one
-                // compare: |d0|^2 is 0 only when d0 is, for offsets above
-                // 1e-154 m)
-                const bool valid = (R0 != 0.0) & (j != self);
                 if (KSTAR && j == self)
                     p.kstar[a * p.n_src + jt] = 0;
                 // LDS byte address of the source's first record (its first half)
                 const uint32_t src0 =
                     lds_base + (uint32_t)(cb * 2 * hrec + s * D) * (uint32_t)sizeof(double2);
-                auto rec_at = [&](uint32_t o) {
-                    const dv2 va = *(lds_dv2)(uintptr_t)o, vb = *(lds_dv2)(uintptr_t)(o + hbytes);
-                    return make_double4(va.x, va.y, vb.x, vb.y);
+                // the target's offset d = r - w_b from a sample and its
+                // sign-test value L^2 - |d|^2
+                auto value_at = [&](uint32_t o, double3 &d) {
+                    const dv2 xy = *(lds_dv2)(uintptr_t)o, zl = *(lds_dv2)(uintptr_t)(o + hbytes);
+                    d = make_double3(rx - xy.x, ry - xy.y, rz - zl.x);
+                    return lightcone_value(d, zl.y);
                 };
-                auto rec = [&](int b) { return rec_at(src0 + (uint32_t)b * (uint32_t)sizeof(double2)); };
-                auto value = [&](double4 r) { return lightcone_value(r, d0x, d0y, d0z); };
-                auto test = [&](int b) { return value(rec(b)) > R0; };
+                auto addr = [&](int b) { return src0 + (uint32_t)b * (uint32_t)sizeof(double2); };
+                auto test = [&](int b) {
+                    double3 d;
+                    return value_at(addr(b), d) > 0.0;
+                };
 
-                int g;        // the bracket's older end, D - 1 before the history
-                double4 r1;   // its record
-                double q1;    // and sign-test value
-                bool before;  // the retarded time precedes the history
-                // the guessed slot of a guided search
+                // the guessed slot
+                float k_slot;  // 1 / curvature of the sign-test value in the slot
                 auto guess_of = [&]() -> float {
-                    if constexpr (kLine) {
-                        const float4 l = line[cb * TS + s];
-                        const float b = __builtin_fmaf((float)d0x, l.x, __builtin_fmaf((float)d0y, l.y, (float)d0z * l.z));
-                        const float gf = b + __builtin_amdgcn_sqrtf(__builtin_fmaf(b, b, l.w * (float)R0));
+                    const float4 l0 = line[(cb * TS + s) * 2], l1 = line[(cb * TS + s) * 2 + 1];
+                    const float dx = rfx - l0.x, dy = rfy - l0.y, dz = rfz - l0.z;
+                    const float r2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
+                    k_slot = l0.w;
+                    if constexpr (GUESS == 4) {
+                        return kcur >= 1 && kcur < D ? (float)kcur : (float)(D - 1);
+                    } else if constexpr (GUESS == 3) {
+                        // surrogate per pair: predicted c (t - t_r) / |r - w_n| times the distance
+                        return p.G[jt * p.g_groups + grp_index] * __builtin_amdgcn_sqrtf(r2) * inv_cdt;
+                    } else {
+                        const float b = __builtin_fmaf(dx, l1.x, __builtin_fmaf(dy, l1.y, dz * l1.z));
+                        const float gf = b + __builtin_amdgcn_sqrtf(__builtin_fmaf(b, b, l0.w * r2));
                         // surrogate, one evaluation per group: the group's
                         // correction factor to straight-line motion
                         return GUESS == 1 ? gf * gcorr[(cb * kWaves + wave) * TS + s] : gf;
-                    } else if constexpr (GUESS == 4) {
-                        return kcur >= 1 && kcur < D ? (float)kcur : (float)(D - 1);
-                    } else {
-                        // surrogate per pair: predicted c (t - t_r) / |r - w_n| times the distance
-                        return p.G[jt * p.g_groups + grp_index] * __builtin_amdgcn_sqrtf((float)R0) * inv_cdt;
                     }
                 };
+                int g;           // the bracket's older end, D - 1 before the history
+                double3 d1;      // the target's offset from it
+                double q0, q1;   // sign-test values of its newer and older end
+                bool before;     // the retarded time precedes the history
+                auto bracket_at = [&](int at) {
+                    double3 d;
+                    g = at;
+                    q0 = value_at(addr(g - 1), d);
+                    q1 = value_at(addr(g - 1) + (uint32_t)sizeof(double2), d1);
+                };
+                const bool other = j != self;
                 if constexpr (COUNT || (kChord && KSTAR)) {
                     // The mode's search in its plain form, whose sign tests
                     // are counted: the paper's bisection (the halvings of the
@@ -599,35 +560,28 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                             b = in_range ? k : -1;
                             n = was_before || k == 1 ? 1 : 2;
                         }
-                        if (!hit && valid)
+                        if (!hit && other)
                             b = search_guided(test, D, guess_of(), 6, n, fb);
                     }
-                    if (COUNT && valid) {
+                    if (COUNT && other) {
                         probes += n;
                         nfall += fb;
                     }
                     before = b < 0;
-                    g = before ? D - 1 : b;
-                    r1 = rec(g);
-                    q1 = value(r1);
+                    bracket_at(before ? D - 1 : b);
                 } else {
                     // A guessed bracket, confirmed by the two samples that
                     // define it, in every lane; lanes that miss get one more
                     // guess from the two values, and a wavefront with a lane
                     // that still misses bisects, all lanes in step.
-                    bool in1, miss = true;
+                    bool miss = other;
                     if (bisect_left == 0) {
                         const float last = (float)(D - 1);
-                        double q0;
                         auto confirm = [&](float guess) {
-                            g = (int)__builtin_amdgcn_fmed3f(__builtin_ceilf(guess), 1.0f, last);
-                            const uint32_t o = src0 + (uint32_t)(g - 1) * (uint32_t)sizeof(double2);
-                            q0 = value(rec_at(o));
-                            r1 = rec_at(o + (uint32_t)sizeof(double2));
-                            q1 = value(r1);
-                            in1 = q1 > R0;
+                            bracket_at((int)__builtin_amdgcn_fmed3f(__builtin_ceilf(guess), 1.0f, last));
                             // hit: (in, out), or the oldest sample out
-                            miss = valid & ((in1 & (q0 > R0)) | (!in1 & (g != D - 1)));
+                            const bool in1 = q1 > 0.0;
+                            miss = other & ((in1 & (q0 > 0.0)) | (!in1 & (g != D - 1)));
                         };
                         confirm(guess_of());
                         if (any_lane(miss)) {
@@ -636,8 +590,8 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                             // pair with the chord's curvature give the next
                             // guess.
                             if (miss) {
-                                const float curv = (float)rec(D - 1).w * __builtin_amdgcn_rcpf(last * last);
-                                const float F = (float)(q1 - R0), S = (float)(q1 - q0) + curv;
+                                const float curv = __builtin_amdgcn_rcpf(k_slot);
+                                const float F = (float)q1, S = (float)(q1 - q0) + curv;
                                 confirm((float)g - 2.0f * F *
                                                        __builtin_amdgcn_rcpf(S + __builtin_amdgcn_sqrtf(__builtin_fmaf(
                                                                                      S, S, -4.0f * curv * F))));
@@ -649,33 +603,36 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         }
                     } else {
                         --bisect_left;
-                        miss = valid;
                     }
                     if (any_lane(miss)) {
                         // The paper's search: the oldest sample, then the
                         // halvings of the whole history, their widths uniform
                         // across lanes (extra halvings of a one-step bracket
                         // change nothing).
-                        in1 = test(D - 1);
+                        const bool in_hist = test(D - 1);
                         uint32_t xo = src0;  // f(xo) <= 0, the bracket lies in (xo, xo + n]
-                        if (any_lane(in1 & valid)) {
+                        if (any_lane(in_hist & other)) {
                             int n = D - 1;
                             do {
 #pragma unroll
                                 for (int k = 0; k < 3; ++k) {
                                     const int half = n >> 1;
                                     const uint32_t mo = xo + (uint32_t)half * (uint32_t)sizeof(double2);
-                                    xo = value(rec_at(mo)) > R0 ? xo : mo;
+                                    double3 d;
+                                    xo = value_at(mo, d) > 0.0 ? xo : mo;
                                     n -= half;
                                 }
                             } while (n > 1);
                         }
-                        g = in1 ? (int)((xo - src0) / (uint32_t)sizeof(double2)) + 1 : D - 1;
-                        r1 = rec(g);
-                        q1 = value(r1);
+                        bracket_at(in_hist ? (int)((xo - src0) / (uint32_t)sizeof(double2)) + 1 : D - 1);
                     }
-                    before = !in1;
+                    before = !(q1 > 0.0);
                 }
+                // A target on the source's newest position (eta = 0) has the
+                // value 0 there and the bracket next to it.
+                bool valid = other;
+                if (any_lane(q0 == 0.0))
+                    valid = other & !((q0 == 0.0) & (g == 1));
                 // the bracket's velocity records: uniform row base plus 32-bit
                 // lane offsets
                 uint32_t o1, o2;  // byte offsets of the two records in the source's row
@@ -687,22 +644,21 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                     int ph1 = p.head - g;
                     ph1 += ph1 < 0 ? D : 0;
                     const int ph2 = ph1 + 1 == D ? 0 : ph1 + 1;
-                    o1 = (uint32_t)ph1 * (uint32_t)sizeof(double4);
-                    o2 = (uint32_t)ph2 * (uint32_t)sizeof(double4);
+                    o1 = (uint32_t)ph1 * (uint32_t)sizeof(double2);
+                    o2 = (uint32_t)ph2 * (uint32_t)sizeof(double2);
                 }
-                const int64_t row = jt * D * (int64_t)sizeof(double4);
-                auto at = [&](const double4 *ring, uint32_t o) {
-                    return *reinterpret_cast<const double4 *>(reinterpret_cast<const char *>(ring) + row + o);
-                };
-                const double4 v1 = at(p.ring_v, o1);
-                // r - w_1 = d0 + D from the staged -2 D
-                const double3 d1 = make_double3(__builtin_fma(-0.5, r1.x, d0x), __builtin_fma(-0.5, r1.y, d0y),
-                                                __builtin_fma(-0.5, r1.z, d0z));
+                const char *row = reinterpret_cast<const char *>(p.vel.plane + jt * D);
+                const int64_t pl = p.vel.n * (int64_t)sizeof(double2);
+                auto at = [&](int k, uint32_t o) { return *reinterpret_cast<const double2 *>(row + k * pl + o); };
+                const double2 u0 = at(0, o1);
                 bool ok;
                 if constexpr (MIX) {
                     float f[6];
                     bool resc = false;
-                    ok = lw_pair_mixed<GUESS == 0>(Ls[g], MixedPair{d1, v1, at(p.ring_v, o2)}, before, (float)p.kq, f, resc);
+                    const double2 u3 = at(3, o1), w0 = at(0, o2), w3 = at(3, o2);  // plane 3: {1/h, v_z}
+                    ok = lw_pair_mixed<GUESS == 0>(Ls[g], MixedPair{d1, make_double4(u0.x, u0.y, u3.y, u3.x),
+                                                                   make_double4(w0.x, w0.y, w3.y, 0.0)},
+                                                   before, (float)p.kq, f, resc);
                     if (COUNT && valid)
                         nresc += resc ? 1 : 0;
                     if (valid && ok) {
@@ -711,17 +667,21 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                             acc[k] += f[k];
                     }
                 } else {
-                    const double4 sg1 = at(p.seg, o1);
-                    const double3 acc1 = make_double3(zero_if(before, sg1.x), zero_if(before, sg1.y), zero_if(before, sg1.z));
+                    const double2 u1 = at(1, o1), u2 = at(2, o1);
+                    const double3 v1 = make_double3(u0.x, u0.y, u1.x);
+                    const double3 acc1 = make_double3(zero_if(before, u1.y), zero_if(before, u2.x), zero_if(before, u2.y));
                     double3 E, h, vr;
                     double en;
                     if constexpr (MID) {
-                        // w_2 - w_1 = D_1 - D_2 from the staged -2 D of both ends
-                        const double4 r2 = rec(g - 1), v2 = at(p.ring_v, o2);
-                        const double3 dw = make_double3(-0.5 * (r1.x - r2.x), -0.5 * (r1.y - r2.y), -0.5 * (r1.z - r2.z));
-                        ok = lw_pair<MID>(d1, q1 - R0, Ls[g], v1, acc1, sg1.w, E, h, en, vr, !before, v2, dw);
+                        // w_2 - w_1 from the offsets from both ends
+                        double3 d2;
+                        (void)value_at(addr(g - 1), d2);
+                        const double3 dw = make_double3(d1.x - d2.x, d1.y - d2.y, d1.z - d2.z);
+                        const double2 w0 = at(0, o2);
+                        const double3 v2 = make_double3(w0.x, w0.y, at(3, o2).y);
+                        ok = lw_pair<MID>(d1, q1, Ls[g], v1, acc1, E, h, en, vr, !before, v2, dw);
                     } else {
-                        ok = lw_pair<MID>(d1, q1 - R0, Ls[g], v1, acc1, sg1.w, E, h, en, vr, false, v1, d1);
+                        ok = lw_pair<MID>(d1, q1, Ls[g], v1, acc1, E, h, en, vr, false, v1, d1);
                     }
                     if (valid && ok) {
                         acc[0] += E.x;
@@ -739,7 +699,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                     }
                 }
                 // a coincident pair that is not left out, or a failed root
-                const bool failed = (j != self) & !(valid & ok);
+                const bool failed = other & !(valid & ok);
                 if (any_lane(failed) && failed)
                     fail_j = min(fail_j, j);
                 // (kept out of the way of the loads: their wait is in order)
@@ -770,7 +730,6 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                 in_acc = 0;
             }
         }
-        cur3 = next3(cur3);
         if (DB) {
             cb ^= 1;
             __syncthreads();
@@ -820,7 +779,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             }
         }
         if (fail_j != INT32_MAX)
-            report_error(p.err, tgt, fail_j, kErrCoincident);
+            report_error(p.err, !p.x && p.order ? (int64_t)p.order[a] : a, fail_j, kErrCoincident);
     }
     if (ADAPT) {
         // one atomic pair per wavefront

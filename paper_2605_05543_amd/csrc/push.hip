@@ -7,22 +7,76 @@
 
 namespace empp {
 
-// Segment records of every (source, slot) from the velocity ring (a ring
-// read from a checkpoint; the newest slot has no segment).
-__global__ void segments_kernel(const double4 *ring_v, int64_t N, int D, double4 *seg)
+// Velocity records {v, 1/h} as checkpoints hold them: records q0 .. q0 + n - 1
+// of the ring to or from rec.
+__global__ void vel_pack_kernel(VelRing vel, int64_t q0, int64_t n, double4 *rec)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n)
+        return;
+    const double3 v = vel.v(q0 + k);
+    rec[k] = make_double4(v.x, v.y, v.z, vel.inv_h(q0 + k));
+}
+
+__global__ void vel_unpack_kernel(const double4 *rec, int64_t q0, int64_t n, VelRing vel)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n)
+        return;
+    const double4 r = rec[k];
+    vel.set_v(q0 + k, make_double3(r.x, r.y, r.z), r.w);
+}
+
+// Accelerations of every (source, slot) from the velocities (a ring read
+// from a checkpoint; the newest slot has no segment).
+__global__ void vel_accel_kernel(VelRing vel, int64_t N, int D)
 {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= N * (int64_t)D)
         return;
     const int64_t j = q / D;
     const int ph = (int)(q - j * D);
-    seg[q] = segment_record(ring_v[q], ring_v[j * D + (ph + 1 == D ? 0 : ph + 1)]);
+    vel.set_a(q, vel.v(q), vel.v(j * D + (ph + 1 == D ? 0 : ph + 1)), vel.inv_h(q));
 }
 
-hipError_t launch_segments(const double4 *ring_v, int64_t N, int D, double4 *seg, hipStream_t s)
+// Guess data of every source of a history that was set.
+__global__ void guess_lines_kernel(const double4 *ring_w, VelRing vel, const double *T, int64_t N, int D, int head,
+                                   double dt, GuessLine *lines)
 {
-    const int64_t n = N * (int64_t)D;
-    hipLaunchKernelGGL(segments_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ring_v, N, D, seg);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N)
+        return;
+    const int oldest = head + 1 == D ? 0 : head + 1, before = head == 0 ? D - 1 : head - 1;
+    const double4 w = ring_w[i * D + head], wo = ring_w[i * D + oldest], ref = ring_w[before];
+    const double3 wn = make_double3(w.x, w.y, w.z), r0 = make_double3(ref.x, ref.y, ref.z);
+    lines[i] = chord_line(wn, make_double3(wo.x, wo.y, wo.z), kC_LIGHT * (T[head] - T[oldest]), D, r0);
+    lines[N + i] = straight_line(wn, vel.v(i * D + head), dt, r0);
+}
+
+static dim3 blocks_of(int64_t n) { return dim3((unsigned)((n + 255) / 256)); }
+
+hipError_t launch_vel_pack(VelRing vel, int64_t q0, int64_t n, double4 *rec, hipStream_t s)
+{
+    hipLaunchKernelGGL(vel_pack_kernel, blocks_of(n), dim3(256), 0, s, vel, q0, n, rec);
+    return hipGetLastError();
+}
+
+hipError_t launch_vel_unpack(const double4 *rec, int64_t q0, int64_t n, VelRing vel, hipStream_t s)
+{
+    hipLaunchKernelGGL(vel_unpack_kernel, blocks_of(n), dim3(256), 0, s, rec, q0, n, vel);
+    return hipGetLastError();
+}
+
+hipError_t launch_vel_accel(VelRing vel, int64_t N, int D, hipStream_t s)
+{
+    hipLaunchKernelGGL(vel_accel_kernel, blocks_of(N * (int64_t)D), dim3(256), 0, s, vel, N, D);
+    return hipGetLastError();
+}
+
+hipError_t launch_guess_lines(const double4 *ring_w, VelRing vel, const double *T, int64_t N, int D, int head, double dt,
+                              GuessLine *lines, hipStream_t s)
+{
+    hipLaunchKernelGGL(guess_lines_kernel, blocks_of(N), dim3(256), 0, s, ring_w, vel, T, N, D, head, dt, lines);
     return hipGetLastError();
 }
 
@@ -147,20 +201,28 @@ __device__ inline void push_particle(const PushParams &p, int64_t i, double Ex, 
     const double c = kC_LIGHT;
     double g = sqrt(1.0 + (ux * ux + uy * uy + uz * uz) / (c * c));
     double ig = 1.0 / g;
-    // velocity records carry 1/(T_{k+1} - T_k) of their segment in .w
-    // (0 for the newest slot, which has no segment yet)
-    double4 vn = make_double4(ux * ig, uy * ig, uz * ig, 1.0 / (p.t_next - p.t_now));
-    p.ring_v[i * D + p.head] = vn;
+    // velocity records carry 1/(T_{k+1} - T_k) of their segment (0 for the
+    // newest slot, which has no segment yet)
+    const double3 vn = make_double3(ux * ig, uy * ig, uz * ig);
+    const double ih = 1.0 / (p.t_next - p.t_now);
+    p.vel.set_v(i * D + p.head, vn, ih);
+    p.vel.set_a(i * D + p.head, vn, vn, ih);
     int nh = p.head + 1 == D ? 0 : p.head + 1;
     // the segment that ends at this slot has its final velocity; the one
     // that starts here has no acceleration before the next push
     const int ph = p.head == 0 ? D - 1 : p.head - 1;
     if (ph != nh)
-        p.seg[i * D + ph] = segment_record(p.ring_v[i * D + ph], vn);
-    p.seg[i * D + p.head] = p.seg[i * D + nh] = segment_record(vn, vn);
-    p.ring_w[i * D + nh] = make_double4(y.x + vn.x * p.dt, y.y + vn.y * p.dt, y.z + vn.z * p.dt, 0.0);
-    vn.w = 0.0;
-    p.ring_v[i * D + nh] = vn;
+        p.vel.set_a(i * D + ph, p.vel.v(i * D + ph), vn, p.vel.inv_h(i * D + ph));
+    const double3 wn = make_double3(y.x + vn.x * p.dt, y.y + vn.y * p.dt, y.z + vn.z * p.dt);
+    p.ring_w[i * D + nh] = make_double4(wn.x, wn.y, wn.z, 0.0);
+    // guess data of the next pass
+    const int oldest = nh + 1 == D ? 0 : nh + 1;
+    const double4 wo = p.ring_w[i * D + oldest], ref = p.ring_w[p.head];
+    const double3 r0 = make_double3(ref.x, ref.y, ref.z);
+    p.lines[i] = chord_line(wn, make_double3(wo.x, wo.y, wo.z), c * (p.t_next - p.T[oldest]), D, r0);
+    p.lines[p.N + i] = straight_line(wn, vn, p.dt_cfg, r0);
+    p.vel.set_v(i * D + nh, vn, 0.0);
+    p.vel.set_a(i * D + nh, vn, vn, 0.0);
 }
 
 // A step's merge and push in one launch: a block merges the six components
@@ -213,7 +275,7 @@ __global__ __launch_bounds__(64 * SL) void merge_push_kernel(PushParams p)
 
 // Straight-line prior history: logical slot k = -(D-1)..0 (physical
 // index k + D - 1) at T_k = t0 + k dt, w_k = r + v0 (k dt), v_k = v0.
-__global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double4 *seg, double *T, const double *r,
+__global__ void init_straight_kernel(double4 *ring_w, VelRing vel, double *T, const double *r,
                                      const double *u, int64_t N, int D, double t0, double dt)
 {
     // Rounded exactly as a plain IEEE evaluation (no fused multiply-add),
@@ -232,9 +294,9 @@ __global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double4 *
     double kdt = (double)k * dt;
     ring_w[idx] = make_double4(r[i] + vx * kdt, r[N + i] + vy * kdt, r[2 * N + i] + vz * kdt, 0.0);
     double inv_h = s + 1 < D ? 1.0 / ((t0 + (double)(k + 1) * dt) - (t0 + kdt)) : 0.0;
-    const double4 vr = make_double4(vx, vy, vz, inv_h);
-    ring_v[idx] = vr;
-    seg[idx] = segment_record(vr, vr);
+    const double3 v = make_double3(vx, vy, vz);
+    vel.set_v(idx, v, inv_h);
+    vel.set_a(idx, v, v, inv_h);
     if (i == 0)
         T[s] = t0 + kdt;
 }
@@ -242,7 +304,7 @@ __global__ void init_straight_kernel(double4 *ring_w, double4 *ring_v, double4 *
 // [ns][3][N] component-major history (oldest first) -> ring layout with
 // logical slot s at physical slot s (head = D - 1).
 __global__ void history_to_ring_kernel(const double *w, const double *v, const double *T, double4 *ring_w,
-                                       double4 *ring_v, double4 *seg, int64_t N, int D)
+                                       VelRing vel, int64_t N, int D)
 {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= N * D)
@@ -253,14 +315,14 @@ __global__ void history_to_ring_kernel(const double *w, const double *v, const d
     const double *vs = v + s * 3 * N;
     ring_w[idx] = make_double4(ws[i], ws[N + i], ws[2 * N + i], 0.0);
     double inv_h = s + 1 < D ? 1.0 / (T[s + 1] - T[s]) : 0.0;
-    const double4 v1 = make_double4(vs[i], vs[N + i], vs[2 * N + i], inv_h);
+    const double3 v1 = make_double3(vs[i], vs[N + i], vs[2 * N + i]);
     const double *v2 = s + 1 < D ? vs + 3 * N : vs;
-    ring_v[idx] = v1;
-    seg[idx] = segment_record(v1, make_double4(v2[i], v2[N + i], v2[2 * N + i], 0.0));
+    vel.set_v(idx, v1, inv_h);
+    vel.set_a(idx, v1, make_double3(v2[i], v2[N + i], v2[2 * N + i]), inv_h);
 }
 
 // Ring -> [D][3][N] oldest first (logical order).
-__global__ void ring_to_history_kernel(const double4 *ring_w, const double4 *ring_v, double *w, double *v,
+__global__ void ring_to_history_kernel(const double4 *ring_w, VelRing vel, double *w, double *v,
                                        int64_t N, int D, int head)
 {
     int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -271,7 +333,7 @@ __global__ void ring_to_history_kernel(const double4 *ring_w, const double4 *rin
     int ph = head - (D - 1 - s);
     ph += ph < 0 ? D : 0;
     double4 a = ring_w[i * D + ph];
-    double4 b = ring_v[i * D + ph];
+    double3 b = vel.v(i * D + ph);
     double *ws = w + (int64_t)s * 3 * N;
     double *vs = v + (int64_t)s * 3 * N;
     ws[i] = a.x;
@@ -471,29 +533,29 @@ hipError_t launch_push(const PushParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_init_straight(double4 *rw, double4 *rv, double4 *seg, double *T, const double *r, const double *u, int64_t N,
+hipError_t launch_init_straight(double4 *rw, VelRing vel, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s)
 {
     int64_t tot = N * D;
-    hipLaunchKernelGGL(init_straight_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, rv, seg, T, r, u,
+    hipLaunchKernelGGL(init_straight_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, vel, T, r, u,
                        N, D, t0, dt);
     return hipGetLastError();
 }
 
-hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, double4 *rv,
-                                  double4 *seg, int64_t N, int D, hipStream_t s)
+hipError_t launch_history_to_ring(const double *w, const double *v, const double *T, double4 *rw, VelRing vel,
+                                  int64_t N, int D, hipStream_t s)
 {
     int64_t tot = N * D;
     hipLaunchKernelGGL(history_to_ring_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, w, v, T, rw,
-                       rv, seg, N, D);
+                       vel, N, D);
     return hipGetLastError();
 }
 
-hipError_t launch_ring_to_history(const double4 *rw, const double4 *rv, double *w, double *v, int64_t N, int D,
+hipError_t launch_ring_to_history(const double4 *rw, VelRing vel, double *w, double *v, int64_t N, int D,
                                   int head, hipStream_t s)
 {
     int64_t tot = N * D;
-    hipLaunchKernelGGL(ring_to_history_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, rv, w, v,
+    hipLaunchKernelGGL(ring_to_history_kernel, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rw, vel, w, v,
                        N, D, head);
     return hipGetLastError();
 }
