@@ -27,7 +27,8 @@ hipError_t launch_vel_unpack(const double4 *rec, int64_t q0, int64_t n, VelRing 
 hipError_t launch_vel_accel(VelRing vel, int64_t N, int D, hipStream_t s);
 hipError_t launch_guess_lines(const double4 *ring_w, VelRing vel, const double *T, int64_t N, int D, int head, double dt,
                               GuessLine *lines, hipStream_t s);
-hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, hipStream_t s);
+hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, int64_t stride,
+                               hipStream_t s);
 hipError_t launch_push(const PushParams &p, hipStream_t s);
 hipError_t launch_init_straight(double4 *rw, VelRing vel, double *T, const double *r, const double *u, int64_t N,
                                 int D, double t0, double dt, hipStream_t s);
@@ -51,7 +52,8 @@ hipError_t launch_mlp_sample(const SampleParams &p, const int64_t *tgt, const in
 hipError_t launch_mlp_group_guess(const MlpPacked *net, const GuessParams &p, float *G, hipStream_t s);
 hipError_t launch_group_centroid(const double4 *ring_w, const int32_t *order, int64_t N, int D, int head,
                                  double3 *centroid, hipStream_t s);
-hipError_t launch_group_centroid_x(const double *x, int64_t m, int group, double3 *centroid, hipStream_t s);
+hipError_t launch_group_centroid_x(const double *x, int64_t stride, int64_t m, int group, double3 *centroid,
+                                   hipStream_t s);
 hipError_t launch_merge_centroids(const double3 *cent64, int64_t m, int ratio, double3 *out, hipStream_t s);
 size_t noalloc_scratch_bytes();
 hipError_t noalloc_scratch(int device, void **out);
@@ -135,15 +137,12 @@ std::vector<int32_t> morton_order(const double *x, int64_t N)
     return order;
 }
 
+// Source chunks a context's partials are laid out for (N targets), and the
+// allocation-free call's limit is stated with.
 int splits_for(const empp_config &c)
 {
     if (c.source_splits > 0)
         return std::min(c.source_splits, kMaxSplits);
-    // About 8192 blocks of the FP64 pair kernel (32 rounds of one block per
-    // CU) evens out blocks that finish early and keeps each chunk's
-    // histories near its XCD's L2 (measured optimum at N = 65536: 128
-    // chunks); the warm-started search, with less work per tile, does best
-    // with half as many.
     int64_t bx = (c.n + kBlockFp64 - 1) / kBlockFp64;
     const int tile = std::min(4, std::max(1, 2048 / c.depth));
     const int64_t target = c.guess == EMPP_GUESS_PREVIOUS ? 4096 : 8192;
@@ -151,6 +150,96 @@ int splits_for(const empp_config &c)
     int64_t maxs = std::max<int64_t>(1, c.n / (4 * tile));
     int64_t s = std::min(want, maxs);
     return (int)std::max<int64_t>(1, std::min<int64_t>(s, kMaxSplits));
+}
+
+// Rows of partials the layout holds for N targets: the nominal chunks, and
+// for a few thousand particles as many as fill the chip with blocks.
+int part_rows(const empp_config &c)
+{
+    const int64_t bx = (c.n + kBlockFp64 - 1) / kBlockFp64;
+    return (int)std::max<int64_t>(splits_for(c), std::min((256 + bx - 1) / bx, c.n));
+}
+
+// How a launch of m targets is cut: wavefronts that share a target's sources
+// (log2) and source chunks.
+struct PairSplit {
+    int sg_log2 = 0, nsplit = 1;
+    int64_t src = 0;  // sources per chunk
+    int run_len = 0;  // mixed precision: see PairParams
+};
+
+// A block has 16 wavefronts: of 1024 targets, or of fewer whose sources go
+// round 2 ... 16 wavefronts each (as many as a tile has sources) and whose sums
+// meet in LDS.  The cut minimises the launch's time, counted in steps of one
+// source (1.3 us for a block of 16 wavefronts at D = 512): rounds of 256 blocks,
+// one a CU, times a wavefront's sources, a third of a step per staged tile and
+// four to start; the merge, 96 bytes per chunk and target at 4 TB/s and the
+// wait for its rows; 2 % of a block for the spread of the last round.  Where a
+// chunk's target blocks take more than one turn of an XCD's 32 CUs, 1.5 % more
+// if the chunks in flight, one per XCD, miss the 256 MiB cache behind the L2s.
+// Steps, D = 512, us: N = 1024, 64 chunks and one wavefront (64 blocks) 40.8,
+// two 30.6, four (256 blocks) 26.3, 128 chunks and four 30.8; N = 3000, 84
+// chunks (252 blocks) 74.7, 96 (288 blocks) 117; N = 8192, 32 chunks (256
+// blocks) 417, 256 500, 512 (the nominal chunks) 621; N = 16384, 16 chunks
+// 1588, 256 1773.  ms: N = 40000, D = 256, 16 chunks (640 blocks) 10.0, 64 8.40;
+// N = 65536, 64 chunks of 1024 sources 24.29, 128 of 512 23.87.  64 targets of
+// 8192 sources, 256 chunks: one wavefront 51 us, four 38.5.
+//
+// In mixed precision the FP32 sums of a target are merged where the nominal
+// chunks end and after every 8 sources from there, whatever the launch's
+// chunks are, so that results do not depend on them: chunks are multiples of
+// the nominal one, or its halves of whole runs of 8, and a target has one
+// wavefront.
+PairSplit pair_split(const empp_config &c, int64_t m)
+{
+    const int nominal = splits_for(c);
+    const int64_t N = c.n, base = (N + nominal - 1) / nominal;
+    m = std::min(m, N);  // a larger call runs N targets at a time
+    const bool mixed = c.precision == EMPP_MIXED;
+    const int64_t ts = pair_fp64_tile(c.depth), waves = (m + 63) / 64;
+    // what the partials hold, here and in the allocation-free call
+    const int64_t room = std::min((int64_t)part_rows(c) * N, std::max((int64_t)nominal * m, (int64_t)1 << 20));
+    const int64_t most = std::max<int64_t>(1, std::min(room / m, (int64_t)kMaxSplits));
+    PairSplit s;
+    double best = INFINITY;
+    auto consider = [&](int sg, int64_t src) {
+        const int64_t rows = (N + src - 1) / src, targets = kBlockFp64 >> sg, nbx = (m + targets - 1) / targets;
+        if (rows > most)
+            return;
+        const double own = (double)((src + (1 << sg) - 1) >> sg), tiles = (double)((src + ts - 1) / ts);
+        // a block of fewer wavefronts takes its steps faster
+        const double step = 0.4 + 0.6 * (double)std::min<int64_t>(16, waves << sg) / 16.0;
+        double t = (double)((nbx * rows + 255) / 256) * (step * own + 0.35 * tiles + 4.0) +
+                   (double)(rows * m) / 60000.0 + (double)rows / 100.0 + 0.02 * own;
+        if (nbx > 32 && ((rows & 7) != 0 || 8 * src * c.depth * 96 > ((int64_t)256 << 20)))
+            t *= 1.015;
+        if (t < best) {
+            best = t;
+            s.sg_log2 = sg;
+            s.src = src;
+        }
+    };
+    for (int sg = 0; sg <= (mixed ? 0 : 4) && (int64_t)1 << sg <= ts; ++sg) {
+        if (c.source_splits > 0) {
+            consider(sg, base);
+            continue;
+        }
+        const int64_t targets = kBlockFp64 >> sg, nbx = (m + targets - 1) / targets;
+        for (int64_t k = 1; k <= 64; ++k) {
+            int64_t rows = std::max<int64_t>(1, std::min(std::min(256 * k / nbx, most), N >> sg));
+            if (nbx > 32 && rows > 8)
+                rows &= ~(int64_t)7;
+            const int64_t src = (N + rows - 1) / rows;
+            consider(sg, mixed ? (src + base - 1) / base * base : src);
+        }
+        consider(sg, base);
+    }
+    if (mixed && c.source_splits <= 0)
+        for (int64_t src = base; src % 16 == 0;)
+            consider(0, src /= 2);
+    s.nsplit = (int)((N + s.src - 1) / s.src);
+    s.run_len = (int)std::min<int64_t>(base, INT32_MAX);
+    return s;
 }
 
 Layout layout_for(const empp_config &c)
@@ -170,7 +259,7 @@ Layout layout_for(const empp_config &c)
     L.u = take(3 * N * sizeof(double));
     L.E = take(3 * N * sizeof(double));
     L.B = take(3 * N * sizeof(double));
-    L.part = take((uint64_t)splits_for(c) * 12 * N * sizeof(double));
+    L.part = take((uint64_t)part_rows(c) * 12 * N * sizeof(double));
     L.err = take(2 * sizeof(unsigned long long));
     L.counters = take(8 * sizeof(unsigned long long));
     L.diag = take(((N + kBlock - 1) / kBlock) * 7 * sizeof(double));
@@ -250,8 +339,10 @@ struct empp_ctx {
     char *ws = nullptr;
     bool owns_ws = false;
     void *scratch = nullptr;  // this device's copy of the allocation-free entry point's scratch
-    int nsplit = 1;
+    int nsplit = 1;  // nominal source chunks
     int tile = 1;
+    int64_t split_m = -1;  // the cut of the last launch and its target count
+    PairSplit split;
     // state
     bool have_bunch = false;
     bool have_history = false;
@@ -354,9 +445,15 @@ empp_status reset_adaptive(empp_ctx *ctx)
     return EMPP_OK;
 }
 
-PairParams pair_params(empp_ctx *ctx)
+PairParams pair_params(empp_ctx *ctx, int64_t m)
 {
     PairParams p{};
+    if (ctx->split_m != m) {
+        ctx->split = pair_split(ctx->cfg, m);
+        ctx->split_m = m;
+    }
+    const PairSplit sp = ctx->split;
+    p.m = m;
     p.ring_w = ctx->ring_w();
     p.vel = ctx->vel();
     p.line = nullptr;
@@ -368,10 +465,11 @@ PairParams pair_params(empp_ctx *ctx)
     const double c = kC_LIGHT;
     const double eps0 = 1.0 / (kMU0 * c * c);
     p.kq = ctx->cfg.q / (4.0 * M_PI * eps0);
-    p.nsplit = ctx->nsplit;
-    p.src_per_split = (ctx->cfg.n + ctx->nsplit - 1) / ctx->nsplit;
+    p.nsplit = sp.nsplit;
+    p.src_per_split = sp.src;
+    p.run_len = sp.run_len;
     p.tile = ctx->tile;
-    p.sg_log2 = 0;
+    p.sg_log2 = sp.sg_log2;
     p.order = nullptr;
     p.part = ctx->part();
     p.err = ctx->err();
@@ -429,7 +527,7 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
     if (ctx->cfg.guess == EMPP_GUESS_MLP_PAIR) {
         // one evaluation per (target, source): the "group" is the target
         return timed(ctx, 2, [&]() {
-            hipError_t e = launch_group_centroid_x(p.x, p.m, 1, cent_pair, ctx->stream);
+            hipError_t e = launch_group_centroid_x(p.x, p.x_stride, p.m, 1, cent_pair, ctx->stream);
             if (e != hipSuccess)
                 return e;
             GuessParams gp{};
@@ -456,7 +554,7 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
         double3 *cent = shift > 6 ? ctx->sg.cent_big : ctx->sg.cent;
         hipError_t e = hipSuccess;
         if (p.x) {
-            e = launch_group_centroid_x(p.x, p.m, 1 << shift, cent, ctx->stream);
+            e = launch_group_centroid_x(p.x, p.x_stride, p.m, 1 << shift, cent, ctx->stream);
         } else {
             // centroids of 64 targets, merged into the larger groups
             e = launch_group_centroid(ctx->ring_w(), p.order, p.m, ctx->cfg.depth, ctx->head, ctx->sg.cent,
@@ -742,11 +840,10 @@ empp_status empp_step(empp_ctx *ctx, int64_t nsteps)
     const double c = kC_LIGHT;
     (void)c;
     for (int64_t s = 0; s < nsteps; ++s) {
-        PairParams p = pair_params(ctx);
+        PairParams p = pair_params(ctx, N);
         p.x = nullptr;
         p.self_index = nullptr;
         p.order = ctx->order();
-        p.m = N;
         p.kstar = nullptr;
         if (ctx->cfg.guess == EMPP_GUESS_PREVIOUS) {
             p.guess = EMPP_GUESS_PREVIOUS;
@@ -770,7 +867,7 @@ empp_status empp_step(empp_ctx *ctx, int64_t nsteps)
         q.B = ctx->B();
         q.part = ctx->part();
         q.order = p.order;
-        q.nsplit = ctx->nsplit;
+        q.nsplit = p.nsplit;
         q.N = N;
         q.D = ctx->cfg.depth;
         q.head = ctx->head;
@@ -829,21 +926,11 @@ static empp_status fields_dev_impl(empp_ctx *ctx, int64_t m, const double *x_dev
     // targets go through in chunks of at most N (the partials buffer's size)
     for (int64_t a0 = 0; a0 < m; a0 += N) {
         const int64_t mc = std::min<int64_t>(N, m - a0);
-        StreamScratch xbuf(ctx->stream), obuf(ctx->stream), gbuf(ctx->stream);
-        // x for the chunk must be a [3][mc] array: chunking needs a copy
-        const double *xc = x_dev;
-        if (m > N) {
-            HIP_TRY(hipMalloc(&xbuf.ptr, 3 * mc * sizeof(double)));
-            double *tmpx = (double *)xbuf.ptr;
-            for (int k = 0; k < 3; ++k)
-                HIP_TRY(hipMemcpyAsync(tmpx + k * mc, x_dev + k * m + a0, mc * sizeof(double),
-                                       hipMemcpyDeviceToDevice, ctx->stream));
-            xc = tmpx;
-        }
-        PairParams p = pair_params(ctx);
-        p.x = xc;
+        StreamScratch gbuf(ctx->stream);
+        PairParams p = pair_params(ctx, mc);
+        p.x = x_dev + a0;
+        p.x_stride = m;
         p.self_index = self_dev ? self_dev + a0 : nullptr;
-        p.m = mc;
         p.kstar = kstar_dev ? kstar_dev + a0 * N : nullptr;
         float *G_pair = nullptr;
         double3 *cent_pair = nullptr;
@@ -853,21 +940,7 @@ static empp_status fields_dev_impl(empp_ctx *ctx, int64_t m, const double *x_dev
             cent_pair = (double3 *)((char *)G_pair + align_up((size_t)mc * N * sizeof(float)));
         }
         HIP_TRY(launch_pair(ctx, p, kstar_dev != nullptr, G_pair, cent_pair));
-        double *Ec = E_dev, *Bc = B_dev;
-        if (m > N) {
-            HIP_TRY(hipMalloc(&obuf.ptr, 6 * mc * sizeof(double)));
-            Ec = (double *)obuf.ptr;
-            Bc = Ec + 3 * mc;
-        }
-        HIP_TRY(launch_merge_fields(ctx->part(), ctx->nsplit, mc, Ec, Bc, ctx->stream));
-        if (m > N) {
-            for (int k = 0; k < 3; ++k) {
-                HIP_TRY(hipMemcpyAsync(E_dev + k * m + a0, Ec + k * mc, mc * sizeof(double), hipMemcpyDeviceToDevice,
-                                       ctx->stream));
-                HIP_TRY(hipMemcpyAsync(B_dev + k * m + a0, Bc + k * mc, mc * sizeof(double), hipMemcpyDeviceToDevice,
-                                       ctx->stream));
-            }
-        }
+        HIP_TRY(launch_merge_fields(ctx->part(), p.nsplit, mc, E_dev + a0, B_dev + a0, m, ctx->stream));
     }
     return EMPP_OK;
 }
@@ -923,20 +996,25 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
                     ctx->nsplit);
     if (!ctx->scratch)
         return fail(EMPP_ESTATE, "no scratch address for device %d", ctx->cfg.device);
-    PairParams p = pair_params(ctx);
-    p.x = x_dev;
-    p.self_index = self_dev;
-    p.m = m;
-    p.kstar = kstar_dev;
-    p.part = reinterpret_cast<double *>(ctx->scratch);
-    // launched directly: no timing events, no guess buffers
-    set_guess_line(ctx, p);
-    hipError_t e = ctx->cfg.precision == EMPP_MIXED
-                       ? launch_pair_mixed(p, ctx->stream, kstar_dev != nullptr, ctx->counting)
-                       : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
-    if (e != hipSuccess)
-        return fail(EMPP_EDEVICE, "pair pass: %s", hipGetErrorString(e));
-    HIP_TRY(launch_merge_fields(p.part, ctx->nsplit, m, E_dev, B_dev, ctx->stream));
+    // N targets at a time, as in empp_fields_at_dev (the same chunks)
+    const int64_t N = ctx->cfg.n;
+    for (int64_t a0 = 0; a0 < m; a0 += N) {
+        const int64_t mc = std::min(N, m - a0);
+        PairParams p = pair_params(ctx, mc);
+        p.x = x_dev + a0;
+        p.x_stride = m;
+        p.self_index = self_dev ? self_dev + a0 : nullptr;
+        p.kstar = kstar_dev ? kstar_dev + a0 * N : nullptr;
+        p.part = reinterpret_cast<double *>(ctx->scratch);
+        // launched directly: no timing events, no guess buffers
+        set_guess_line(ctx, p);
+        hipError_t e = ctx->cfg.precision == EMPP_MIXED
+                           ? launch_pair_mixed(p, ctx->stream, kstar_dev != nullptr, ctx->counting)
+                           : launch_pair_fp64(p, ctx->stream, kstar_dev != nullptr, ctx->counting);
+        if (e != hipSuccess)
+            return fail(EMPP_EDEVICE, "pair pass: %s", hipGetErrorString(e));
+        HIP_TRY(launch_merge_fields(p.part, p.nsplit, mc, E_dev + a0, B_dev + a0, m, ctx->stream));
+    }
     return EMPP_OK;
 }
 
@@ -1524,6 +1602,7 @@ empp_status empp_set_mode(empp_ctx *ctx, int32_t precision, int32_t guess)
         return fail(EMPP_EUNSUPPORTED, "warm-start brackets need a context created with that guess mode");
     ctx->cfg.precision = precision;
     ctx->cfg.guess = guess;
+    ctx->split_m = -1;
     return EMPP_OK;
 }
 

@@ -116,15 +116,17 @@ struct PairParams {
     int32_t head;       // physical index of the newest slot
     double t;           // present time (== T[head]; the pair kernels read T[head])
     double kq;          // Coulomb constant times source charge
-    // targets: external points x[3][m] (x != nullptr) or the particles'
+    // targets: external points x[k * x_stride + a] (x != nullptr) or the particles'
     // newest positions (x == nullptr, then target a is particle a and the
     // pair (a, a) is skipped).
     const double *x;
+    int64_t x_stride;
     const int64_t *self_index;  // external mode only, may be null
     const int32_t *order;       // step mode: target slot -> particle (spatial order), may be null
     int64_t m;
     int64_t src_per_split;
     int32_t nsplit;
+    int32_t run_len;            // mixed precision: sources after which a plain partial is merged (as well)
     int32_t tile;               // sources staged per LDS tile
     int32_t sg_log2;            // log2 of the wavefronts that share a target's sources
     double *part;               // [nsplit][12][m] partial (sum, comp)
@@ -190,20 +192,26 @@ struct PushParams {
 
 // Block of a pair-kernel launch -> (target block bx, source chunk split).
 // The grid is one-dimensional, nbx * nsplit blocks.  Workgroups go to the 8
-// XCDs round-robin by linear index; when the chunk count is a multiple of 8
-// every chunk is given to one XCD, so the target blocks that stage its
-// histories run there together and share that XCD's L2.
+// XCDs round-robin by linear index.  A chunk's blocks go to one XCD, so that
+// the target blocks that stage its histories run there together and share its
+// L2: with a multiple of 8 chunks the XCDs take chunk after chunk in turn
+// (N = 65536, D = 512, 128 chunks: 23.87 ms; an eighth of the range each
+// 24.17), else each takes an eighth of the blocks in chunk order (N = 3000, 42
+// chunks of 6 target blocks: 77 us; any order 96, as some XCDs got 36 blocks
+// for their 32 CUs).
 __device__ inline void pair_block_coords(int nbx, int nsplit, int &bx, int &split)
 {
-    const int L = blockIdx.x;
+    const int L = blockIdx.x, xcd = L & 7;
+    int k = L >> 3;
     if ((nsplit & 7) == 0) {
-        const int xcd = L & 7, k = L >> 3;
         const int round = k / nbx;
         split = xcd + 8 * round;
         bx = k - round * nbx;
     } else {
-        split = L / nbx;
-        bx = L - split * nbx;
+        const int total = nbx * nsplit;
+        k += xcd * (total >> 3) + min(xcd, total & 7);
+        split = k / nbx;
+        bx = k - split * nbx;
     }
 }
 

@@ -881,9 +881,9 @@ __global__ void group_centroid_kernel(const double4 *ring_w, const int32_t *orde
     centroid[grp] = make_double3(sx / cnt, sy / cnt, sz / cnt);
 }
 
-// Group centroids of external targets x[3][m] (`group` consecutive per
+// Group centroids of external targets x[k * stride + a] (`group` consecutive per
 // group; group 1 gives each target its own row).
-__global__ void group_centroid_x_kernel(const double *x, int64_t m, int group, double3 *centroid)
+__global__ void group_centroid_x_kernel(const double *x, int64_t stride, int64_t m, int group, double3 *centroid)
 {
     int64_t grp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t ngroups = (m + group - 1) / group;
@@ -896,8 +896,8 @@ __global__ void group_centroid_x_kernel(const double *x, int64_t m, int group, d
         if (a >= m)
             break;
         sx += x[a];
-        sy += x[m + a];
-        sz += x[2 * m + a];
+        sy += x[stride + a];
+        sz += x[2 * stride + a];
         ++cnt;
     }
     centroid[grp] = make_double3(sx / cnt, sy / cnt, sz / cnt);
@@ -1017,10 +1017,11 @@ hipError_t launch_merge_centroids(const double3 *cent64, int64_t m, int ratio, d
     return hipGetLastError();
 }
 
-hipError_t launch_group_centroid_x(const double *x, int64_t m, int group, double3 *centroid, hipStream_t s)
+hipError_t launch_group_centroid_x(const double *x, int64_t stride, int64_t m, int group, double3 *centroid,
+                                   hipStream_t s)
 {
     int64_t ng = (m + group - 1) / group;
-    hipLaunchKernelGGL(group_centroid_x_kernel, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, x, m, group,
+    hipLaunchKernelGGL(group_centroid_x_kernel, dim3((unsigned)((ng + 255) / 256)), dim3(256), 0, s, x, stride, m, group,
                        centroid);
     return hipGetLastError();
 }

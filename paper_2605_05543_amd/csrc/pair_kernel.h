@@ -318,8 +318,8 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     if (active) {
         if (p.x) {
             rx = p.x[a];
-            ry = p.x[p.m + a];
-            rz = p.x[2 * p.m + a];
+            ry = p.x[p.x_stride + a];
+            rz = p.x[2 * p.x_stride + a];
             self = p.self_index ? (int32_t)p.self_index[a] : -1;
         } else {
             const int64_t tgt = p.order ? (int64_t)p.order[a] : a;
@@ -342,7 +342,19 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     Real sum[6] = {0, 0, 0, 0, 0, 0}, comp[6] = {0, 0, 0, 0, 0, 0};
     Real acc[6] = {0, 0, 0, 0, 0, 0};
     constexpr int kPlainRun = MIX ? 8 : 32;  // sources per plain partial
-    int in_acc = 0;
+    // sources left in the plain partial, and after it to the end of the run
+    int left = kPlainRun, run_left = 0;
+    auto next_run = [&]() {
+        left = kPlainRun;
+        if constexpr (MIX) {
+            run_left = run_left == 0 ? p.run_len : run_left;
+            left = min(kPlainRun, run_left);
+            run_left -= left;
+        }
+    };
+    if constexpr (MIX)
+        run_left = p.run_len - (int)(j0 % p.run_len);
+    next_run();
     int probes = 0, nbefore = 0, npairs = 0, nfall = 0, nresc = 0;
     // first (lowest) source of a failing pair; sources number below 2^31
     int32_t fail_j = INT32_MAX;
@@ -718,7 +730,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             // plain partial sums over kPlainRun sources, then one compensated
             // merge (the same cadence for every search mode: results are
             // bit-identical)
-            if (++in_acc == kPlainRun) {
+            if (--left == 0) {
 #pragma unroll
                 for (int k = 0; k < 6; ++k) {
                     if constexpr (MIX)
@@ -727,7 +739,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         neumaier(sum[k], comp[k], acc[k]);
                     acc[k] = 0;
                 }
-                in_acc = 0;
+                next_run();
             }
         }
         if (DB) {

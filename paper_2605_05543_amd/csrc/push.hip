@@ -80,19 +80,19 @@ hipError_t launch_guess_lines(const double4 *ring_w, VelRing vel, const double *
     return hipGetLastError();
 }
 
-// Merge of the pair partials part[nsplit][12][m].  Bound by latency where m
-// is small and by HBM where it is large: a chain of compensated additions per
-// component and target, over nsplit x 2 loads.  A block takes 64 consecutive
-// targets (512-byte rows) and gives every wavefront the chunks sp = w, w + SL,
-// ...; the SL sums are then added in wavefront order: a fixed order, whatever
-// the scheduling.  With one thread per component and target the chain was
-// nsplit long: for 512 chunks 158 us at 64 targets and 254 us at 8192, the push
-// another 7 us; now 12 us, and 111 us with the push (402 MB, 3.6 TB/s).
-// Sum of component k at target a over this wavefront's chunks into red.
-template <int SL>
-__device__ inline void merge_slice(double2 (*red)[64], const double *part, int nsplit, int64_t m, int k, int64_t a)
+// Merge of the pair partials part[nsplit][12][m].  Bound by HBM where m is
+// large, by the few CUs that a block of targets each puts to work where it is
+// small: a chain of compensated additions per component and target, over
+// nsplit x 2 loads.  A block takes TG consecutive targets and SL slices of the
+// chunks, slice w the chunks w, w + SL, ...; the SL sums are then added in
+// order: a fixed order, whatever the scheduling.  Up to kMergeSmall targets it
+// is 16 targets (rows of 128 bytes, one line) and 32 slices (a step of N = 1024
+// with 256 chunks 30 us, with blocks of 64 targets and 16 slices 48), beyond it
+// 64 and four.
+template <int TG, int SL>
+__device__ inline void merge_slice(double2 (*red)[TG], const double *part, int nsplit, int64_t m, int k, int64_t a)
 {
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = threadIdx.x / TG;
     double s = 0.0, c = 0.0;
     if (a < m) {
         const double *at = part + k * m + a;
@@ -103,35 +103,36 @@ __device__ inline void merge_slice(double2 (*red)[64], const double *part, int n
             neumaier(s, c, base[6 * m]);
         }
     }
-    red[w][lane] = make_double2(s, c);
+    red[w][threadIdx.x % TG] = make_double2(s, c);
 }
 
-// The SL wavefronts' sums, in order.
-template <int SL>
-__device__ inline double merge_slices(const double2 (*red)[64], int lane)
+// The SL slices' sums of target t, in order.
+template <int TG, int SL>
+__device__ inline double merge_slices(const double2 (*red)[TG], int t)
 {
     double s = 0.0, c = 0.0;
 #pragma unroll
     for (int w = 0; w < SL; ++w) {
-        const double2 x = red[w][lane];
+        const double2 x = red[w][t];
         neumaier(s, c, x.x);
         c += x.y;
     }
     return s + c;
 }
 
-// Fields of external targets: component blockIdx.y of 64 targets per block.
-template <int SL>
-__global__ __launch_bounds__(64 * SL) void merge_fields_kernel(const double *part, int nsplit, int64_t m, double *E,
-                                                               double *B)
+// Fields of external targets: component blockIdx.y of TG targets per block,
+// written to rows `stride` apart.
+template <int TG, int SL>
+__global__ __launch_bounds__(TG * SL) void merge_fields_kernel(const double *part, int nsplit, int64_t m, double *E,
+                                                               double *B, int64_t stride)
 {
-    __shared__ double2 red[SL][64];
-    const int lane = threadIdx.x & 63, k = blockIdx.y;
-    const int64_t a = (int64_t)blockIdx.x * 64 + lane;
-    merge_slice<SL>(red, part, nsplit, m, k, a);
+    __shared__ double2 red[SL][TG];
+    const int t = threadIdx.x % TG, k = blockIdx.y;
+    const int64_t a = (int64_t)blockIdx.x * TG + t;
+    merge_slice<TG, SL>(red, part, nsplit, m, k, a);
     __syncthreads();
-    if (threadIdx.x < 64 && a < m)
-        (k < 3 ? E + k * m : B + (k - 3) * m)[a] = merge_slices<SL>(red, lane);
+    if (threadIdx.x < TG && a < m)
+        (k < 3 ? E + k * stride : B + (k - 3) * stride)[a] = merge_slices<TG, SL>(red, t);
 }
 
 // Sec. 2.6: B = (mu0/4pi)(3 (M.rhat) rhat - M)/r^3 with M = M0 e_z, written
@@ -226,14 +227,14 @@ __device__ inline void push_particle(const PushParams &p, int64_t i, double Ex, 
 }
 
 // A step's merge and push in one launch: a block merges the six components
-// of 64 targets of the pair launch's order, its first wavefront pushes those
-// particles.
-template <int SL>
-__global__ __launch_bounds__(64 * SL) void merge_push_kernel(PushParams p)
+// of TG targets of the pair launch's order, a thread a component and target,
+// and pushes those particles, a thread each.
+template <int TG, int SL>
+__global__ __launch_bounds__(TG * SL) void merge_push_kernel(PushParams p)
 {
-    __shared__ double2 red[6][SL][64];
-    const int lane = threadIdx.x & 63;
-    const int64_t a = (int64_t)blockIdx.x * 64 + lane;
+    __shared__ double2 red[6][SL][TG];
+    const int t = threadIdx.x % TG;
+    const int64_t a = (int64_t)blockIdx.x * TG + t;
     const bool first = blockIdx.x == 0 && threadIdx.x == 0;
     if (p.ad) {
         // Sec. 2.4: this step's dt from the pair kernel's reductions (the
@@ -254,16 +255,19 @@ __global__ __launch_bounds__(64 * SL) void merge_push_kernel(PushParams p)
         }
     }
     for (int k = 0; k < 6; ++k)
-        merge_slice<SL>(red[k], p.part, p.nsplit, p.N, k, a);
+        merge_slice<TG, SL>(red[k], p.part, p.nsplit, p.N, k, a);
     __syncthreads();
     if (first)
         p.T[p.head + 1 == p.D ? 0 : p.head + 1] = p.t_next;
-    if (threadIdx.x >= 64 || a >= p.N)
+    for (int k = threadIdx.x / TG; k < 6; k += SL)
+        red[k][0][t].x = merge_slices<TG, SL>(red[k], t);
+    __syncthreads();
+    if (threadIdx.x >= TG || a >= p.N)
         return;
     double f[6];
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-        f[k] = merge_slices<SL>(red[k], lane);
+        f[k] = red[k][0][t].x;
     const int64_t i = p.order[a];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -508,28 +512,28 @@ hipError_t launch_transport(const TransportParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-// Wavefronts per 64 targets of a merge: 16 where the launch has few targets
-// (the chain's length counts), 4 where it fills the chip anyway.
-constexpr int64_t kMergeWide = 16384;
+// Targets of a merge up to which its blocks take 16 each.
+constexpr int64_t kMergeSmall = 16384;
 
-hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, hipStream_t s)
+hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double *E, double *B, int64_t stride,
+                               hipStream_t s)
 {
-    const dim3 grid((unsigned)((m + 63) / 64), 6);
-    if (m <= kMergeWide)
-        hipLaunchKernelGGL((merge_fields_kernel<16>), grid, dim3(1024), 0, s, part, nsplit, m, E, B);
+    if (m <= kMergeSmall)
+        hipLaunchKernelGGL((merge_fields_kernel<16, 32>), dim3((unsigned)((m + 15) / 16), 6), dim3(512), 0, s, part,
+                           nsplit, m, E, B, stride);
     else
-        hipLaunchKernelGGL((merge_fields_kernel<4>), grid, dim3(256), 0, s, part, nsplit, m, E, B);
+        hipLaunchKernelGGL((merge_fields_kernel<64, 4>), dim3((unsigned)((m + 63) / 64), 6), dim3(256), 0, s, part,
+                           nsplit, m, E, B, stride);
     return hipGetLastError();
 }
 
 // Merge of the self-field partials into E, B, and the push.
 hipError_t launch_push(const PushParams &p, hipStream_t s)
 {
-    const dim3 grid((unsigned)((p.N + 63) / 64));
-    if (p.N <= kMergeWide)
-        hipLaunchKernelGGL((merge_push_kernel<16>), grid, dim3(1024), 0, s, p);
+    if (p.N <= kMergeSmall)
+        hipLaunchKernelGGL((merge_push_kernel<16, 32>), dim3((unsigned)((p.N + 15) / 16)), dim3(512), 0, s, p);
     else
-        hipLaunchKernelGGL((merge_push_kernel<4>), grid, dim3(256), 0, s, p);
+        hipLaunchKernelGGL((merge_push_kernel<64, 4>), dim3((unsigned)((p.N + 63) / 64)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
