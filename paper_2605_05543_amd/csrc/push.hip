@@ -86,13 +86,15 @@ hipError_t launch_guess_lines(const double4 *ring_w, VelRing vel, const double *
 // nsplit x 2 loads.  A block takes TG consecutive targets and SL slices of the
 // chunks, slice w the chunks w, w + SL, ...; the SL sums are then added in
 // order: a fixed order, whatever the scheduling.  Up to kMergeSmall targets it
-// is 16 targets (rows of 128 bytes, one line) and 32 slices (a step of N = 1024
-// with 256 chunks 30 us, with blocks of 64 targets and 16 slices 48), beyond it
-// 64 and four.
+// is 16 targets (rows of 128 bytes, one line) and 32 slices, or in a step 8
+// slices of each of the six components (a step of N = 1024, 256 chunks: 48 us
+// with blocks of 64 targets and 16 slices, 30 with 16 and 32; the components
+// side by side and not in turn: N = 256 16.1 -> 13.5 us, N = 1024 with 64 chunks
+// 26.5 -> 22.9), beyond it 64 and four.
 template <int TG, int SL>
 __device__ inline void merge_slice(double2 (*red)[TG], const double *part, int nsplit, int64_t m, int k, int64_t a)
 {
-    const int w = threadIdx.x / TG;
+    const int w = threadIdx.x / TG % SL;
     double s = 0.0, c = 0.0;
     if (a < m) {
         const double *at = part + k * m + a;
@@ -227,10 +229,10 @@ __device__ inline void push_particle(const PushParams &p, int64_t i, double Ex, 
 }
 
 // A step's merge and push in one launch: a block merges the six components
-// of TG targets of the pair launch's order, a thread a component and target,
-// and pushes those particles, a thread each.
-template <int TG, int SL>
-__global__ __launch_bounds__(TG * SL) void merge_push_kernel(PushParams p)
+// of TG targets of the pair launch's order, NK at a time side by side, and
+// pushes those particles, a thread each.
+template <int TG, int SL, int NK>
+__global__ __launch_bounds__(TG * SL * NK) void merge_push_kernel(PushParams p)
 {
     __shared__ double2 red[6][SL][TG];
     const int t = threadIdx.x % TG;
@@ -254,12 +256,12 @@ __global__ __launch_bounds__(TG * SL) void merge_push_kernel(PushParams p)
             p.dt_out[0] = dt;
         }
     }
-    for (int k = 0; k < 6; ++k)
+    for (int k = threadIdx.x / (TG * SL); k < 6; k += NK)
         merge_slice<TG, SL>(red[k], p.part, p.nsplit, p.N, k, a);
     __syncthreads();
     if (first)
         p.T[p.head + 1 == p.D ? 0 : p.head + 1] = p.t_next;
-    for (int k = threadIdx.x / TG; k < 6; k += SL)
+    for (int k = threadIdx.x / TG; k < 6; k += SL * NK)
         red[k][0][t].x = merge_slices<TG, SL>(red[k], t);
     __syncthreads();
     if (threadIdx.x >= TG || a >= p.N)
@@ -531,9 +533,9 @@ hipError_t launch_merge_fields(const double *part, int nsplit, int64_t m, double
 hipError_t launch_push(const PushParams &p, hipStream_t s)
 {
     if (p.N <= kMergeSmall)
-        hipLaunchKernelGGL((merge_push_kernel<16, 32>), dim3((unsigned)((p.N + 15) / 16)), dim3(512), 0, s, p);
+        hipLaunchKernelGGL((merge_push_kernel<16, 8, 6>), dim3((unsigned)((p.N + 15) / 16)), dim3(768), 0, s, p);
     else
-        hipLaunchKernelGGL((merge_push_kernel<64, 4>), dim3((unsigned)((p.N + 63) / 64)), dim3(256), 0, s, p);
+        hipLaunchKernelGGL((merge_push_kernel<64, 4, 1>), dim3((unsigned)((p.N + 63) / 64)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
