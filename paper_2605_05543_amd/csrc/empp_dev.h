@@ -233,7 +233,14 @@ struct TransportParams {
     unsigned long long *key;  // [3]
     double *t;                // [1] present time
     int64_t step;
+    // several steps in one launch: the blocks' minima of even and odd steps
+    // [2][kTransportBlocks], the steps that went through them before, and the
+    // word that a wait that gave up sets
+    unsigned long long *slots;
+    int64_t nsteps, sync_step;
+    unsigned long long *fail;
 };
+constexpr int kTransportBlocks = 256;
 
 constexpr unsigned long long kPosInfBits = 0x7FF0000000000000ull;
 

@@ -494,6 +494,136 @@ __global__ void transport_kernel(TransportParams p)
     }
 }
 
+// Step minima of a transport_steps_kernel launch: thread b < gridDim.x waits for
+// block b's minimum of the step that `tag` (the sign bit, else clear in these
+// positive doubles) and `slots` (even or odd steps) name; returns the smallest
+// to every thread.  The wait is bounded (about a second): a thread that gives up
+// sets *fail, the block then returns a negative value and ends its launch.
+constexpr unsigned kTransportSpinLimit = 1u << 20;
+__device__ inline double wait_for_minima(const unsigned long long *slots, unsigned long long tag,
+                                         unsigned long long *fail, double (*wmin)[4])
+{
+    double v = __longlong_as_double((long long)kPosInfBits);
+    if (threadIdx.x < gridDim.x) {
+        unsigned long long x;
+        unsigned spins = 0;
+        while (((x = __hip_atomic_load(&slots[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 63) != tag) {
+            if (++spins > kTransportSpinLimit) {
+                atomicOr(fail, 1ull);
+                break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+        }
+        v = spins > kTransportSpinLimit ? -1.0 : __longlong_as_double((long long)(x & ~(1ull << 63)));
+    }
+    const int w = threadIdx.x >> 6;
+    if (w < kTransportBlocks / 64) {
+        for (int off = 32; off > 0; off >>= 1)
+            v = fmin(v, __shfl_xor(v, off));
+        if ((threadIdx.x & 63) == 0)
+            (*wmin)[w] = v;
+    }
+    __syncthreads();
+    const int nw = min(kTransportBlocks, (int)blockDim.x) >> 6;
+    v = (*wmin)[0];
+    for (int k = 1; k < nw; ++k)
+        v = fmin(v, (*wmin)[k]);
+    return v;
+}
+
+// p.nsteps steps in one launch, one particle a thread, its state and its field
+// (which the step's minimum and the next step's push share) in registers.  A step
+// of transport_kernel is a launch's gap, the loads and a chain of about ten
+// divisions and roots: 7 us at N = 65536, 17 at 262144.  Here a step's only
+// exchange is its minimum: every block stores its own into its slot, with the
+// step's parity in the sign, and reads all of them, one hop and no counter;
+// slots are used by alternate steps, so a block that is a step ahead (it has
+// read every block's previous minimum) overwrites none that is still read.
+// 4.3 us a step at N = 65536, 6.2 at 262144 (of which about 2.4 are the chain; polls
+// without a pause between them 0.5 more).  The launch is cooperative, so every
+// block is resident.
+__global__ __launch_bounds__(1024) void transport_steps_kernel(TransportParams p)
+{
+    __shared__ double wblock[2][16], wall[2][4];
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const bool live = i < p.N, first = i == 0;
+    const double inf = __longlong_as_double((long long)kPosInfBits);
+    const double c = kC_LIGHT;
+    double4 y = make_double4(0.0, 0.0, 0.0, 0.0);
+    double ux = 0.0, uy = 0.0, uz = 0.0, bx = 0.0, by = 0.0, bz = 0.0;
+    if (live) {
+        y = p.pos[i];
+        ux = p.u[i];
+        uy = p.u[p.N + i];
+        uz = p.u[2 * p.N + i];
+        if (p.ext_field == 1)
+            dipole_field(y.x, y.y, y.z, p.dip_k, bx, by, bz);
+    }
+    double kmin = __longlong_as_double((long long)p.key[p.step % 3]), kold = kmin;
+    double t = first ? p.t[0] : 0.0;
+    for (int64_t k = 0; k < p.nsteps; ++k) {
+        double dt = p.dt_max;
+        const double d = p.gyro_k * kmin;
+        if (d < dt)
+            dt = d;
+        t += dt;
+        double v = inf;
+        if (live) {
+            higuera_cary(ux, uy, uz, 0.0, 0.0, 0.0, bx, by, bz, p.q_over_2m * dt);
+            double ig = 1.0 / sqrt(1.0 + (ux * ux + uy * uy + uz * uz) / (c * c));
+            y = make_double4(y.x + ux * ig * dt, y.y + uy * ig * dt, y.z + uz * ig * dt, 0.0);
+            if (p.ext_field == 1) {
+                dipole_field(y.x, y.y, y.z, p.dip_k, bx, by, bz);
+                double g = sqrt(1.0 + (ux * ux + uy * uy + uz * uz) / (c * c));
+                double bm = sqrt(bx * bx + by * by + bz * bz);
+                v = bm > 0.0 ? g / bm : inf;
+            }
+        }
+        for (int off = 32; off > 0; off >>= 1)
+            v = fmin(v, __shfl_xor(v, off));
+        const int par = (int)(k & 1);
+        if ((threadIdx.x & 63) == 0)
+            wblock[par][threadIdx.x >> 6] = v;
+        __syncthreads();
+        const int64_t s = p.sync_step + k;
+        unsigned long long *slots = p.slots + (s & 1) * kTransportBlocks;
+        const unsigned long long tag = (unsigned long long)(s >> 1 & 1);
+        if (threadIdx.x == 0) {
+            double m = fmin(inf, wblock[par][0]);
+            for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
+                m = fmin(m, wblock[par][w]);
+            __hip_atomic_store(&slots[blockIdx.x], (unsigned long long)__double_as_longlong(m) | tag << 63,
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        kold = kmin;
+        kmin = wait_for_minima(slots, tag, p.fail, &wall[par]);
+        if (kmin < 0.0)
+            break;
+    }
+    if (live) {
+        p.pos[i] = y;
+        p.u[i] = ux;
+        p.u[p.N + i] = uy;
+        p.u[2 * p.N + i] = uz;
+    }
+    if (first) {
+        // as transport_kernel leaves them
+        const int64_t last = p.step + p.nsteps - 1;
+        p.key[last % 3] = (unsigned long long)__double_as_longlong(kold);
+        p.key[(last + 1) % 3] = (unsigned long long)__double_as_longlong(kmin);
+        p.key[(last + 2) % 3] = kPosInfBits;
+        p.t[0] = t;
+    }
+}
+
+// No step has gone through the slots yet: all carry the tag of the third step.
+__global__ void transport_slots_kernel(unsigned long long *slots, unsigned long long *fail)
+{
+    slots[threadIdx.x] = kPosInfBits | 1ull << 63;
+    if (threadIdx.x == 0)
+        *fail = 0;
+}
+
 hipError_t launch_handoff(const double4 *ring_w, int D, int head, double4 *pos, const double *u, int64_t N,
                           double dip_k, int ext_field, unsigned long long *key, double *t, double t_now,
                           hipStream_t s)
@@ -506,6 +636,23 @@ hipError_t launch_handoff(const double4 *ring_w, int D, int head, double4 *pos, 
     hipLaunchKernelGGL(transport_key_kernel, dim3(nb), dim3(256), 0, s, (const double4 *)pos, u, N, dip_k,
                        ext_field, key);
     return hipGetLastError();
+}
+
+hipError_t launch_transport_slots(const TransportParams &p, hipStream_t s)
+{
+    hipLaunchKernelGGL(transport_slots_kernel, dim3(1), dim3(2 * kTransportBlocks), 0, s, p.slots, p.fail);
+    return hipGetLastError();
+}
+
+// p.nsteps steps on blocks of `threads` (at most kTransportBlocks of them, all
+// resident).
+hipError_t launch_transport_steps(const TransportParams &p, int threads, hipStream_t s)
+{
+    TransportParams arg = p;
+    void *args[] = {&arg};
+    return hipLaunchCooperativeKernel((const void *)transport_steps_kernel,
+                                      dim3((unsigned)((p.N + threads - 1) / threads)), dim3((unsigned)threads), args, 0,
+                                      s);
 }
 
 hipError_t launch_transport(const TransportParams &p, hipStream_t s)

@@ -1,0 +1,41 @@
+"""Transport steps put into one launch against the same steps in launches of
+one: state, clock, diagnostics and saved files bit for bit, at the edges of
+its blocks (256 ... 1024 threads, up to 256 blocks) and beyond them, for call
+lengths on both sides of the rule in turn, with and without the field."""
+import numpy as np
+import pytest
+
+from paper_2605_05543_amd import bunch
+
+pytestmark = pytest.mark.gpu
+
+Q, ME = -bunch.E_CHARGE, bunch.M_ELECTRON
+B0, RE = 3.12e-5, bunch.R_EARTH
+
+
+@pytest.mark.parametrize("n,field", [(2, 1), (255, 1), (256, 0), (257, 1), (1000, 1), (65536, 1), (65537, 1),
+                                     (262144, 1), (262145, 1)])
+def test_transport_steps_together(n, field, tmp_path):
+    from paper_2605_05543_amd._lib import Context
+
+    print(f"case transport together n={n} field={field}", flush=True)
+    rng = np.random.default_rng(n)
+    r = 1e-3 * rng.standard_normal((3, n))
+    r[0] += 3 * RE
+    u = 3e8 * (0.1 * rng.standard_normal((3, n)) + np.array([[0.0], [1.0], [1.5]]))
+    out = []
+    for together in (True, False):
+        with Context(n=n, depth=2, q=Q, m=ME, dt=1e-13, ext_field=field, dipole_b0=B0, dipole_re=RE) as ctx:
+            ctx.init_bunch(r, u, 0.0)
+            ctx.init_history_straight()
+            ctx.handoff()
+            for k in (7, 1, 5, 4, 12, 6):
+                for _ in range(1 if together else k):
+                    ctx.transport(1e-7, 1 / 32, k if together else 1)
+            res = ctx.state()
+            f = tmp_path / f"{together}.ckpt"
+            if n <= 1000:
+                ctx.save(str(f))
+            out.append((*[np.array(x) for x in res], f.read_bytes() if f.exists() else b""))
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
