@@ -98,7 +98,7 @@ constexpr uint64_t kAlign = 256;
 uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    uint64_t ring_w, vel, lines, T, u, E, B, part, err, counters, diag, order, pos, skey, st, tslots, ad, kc, kc_bytes, total;
+    uint64_t ring_w, vel, lines, T, r, u, E, B, part, err, counters, diag, order, pos, skey, st, tslots, ad, kc, kc_bytes, total;
 };
 
 
@@ -262,18 +262,21 @@ Layout layout_for(const empp_config &c)
     L.vel = take(N * D * 4 * sizeof(double2));
     L.lines = take(2 * N * sizeof(GuessLine));
     L.T = take(D * sizeof(double));
-    L.u = take(3 * N * sizeof(double));
+    // fields, error words, clock, read-back positions and momenta side by side:
+    // one copy takes what a read-back needs
     L.E = take(3 * N * sizeof(double));
     L.B = take(3 * N * sizeof(double));
-    L.part = take((uint64_t)part_rows(c) * 12 * N * sizeof(double));
     L.err = take(2 * sizeof(unsigned long long));
+    L.st = take(2 * sizeof(double));  // Stage II's clock, the word of a wait that gave up
+    L.r = take(3 * N * sizeof(double));
+    L.u = take(3 * N * sizeof(double));
+    L.part = take((uint64_t)part_rows(c) * 12 * N * sizeof(double));
     L.counters = take(8 * sizeof(unsigned long long));
     L.diag = take(((N + kBlock - 1) / kBlock) * 7 * sizeof(double));
     L.order = take(N * sizeof(int32_t));
-    // Stage II: compact positions, the step-minimum slots and the clock
+    // Stage II: compact positions and the step-minimum slots
     L.pos = take(N * sizeof(double4));
     L.skey = take(4 * sizeof(unsigned long long));
-    L.st = take(2 * sizeof(double));  // the clock, the word of a wait that gave up
     L.tslots = take(2 * kTransportBlocks * sizeof(unsigned long long));
     // adaptive step: two {eta_min, v_max^2} slots and the last dt
     L.ad = take(8 * sizeof(unsigned long long));
@@ -348,8 +351,12 @@ struct empp_ctx {
     void *scratch = nullptr;  // this device's copy of the allocation-free entry point's scratch
     int nsplit = 1;  // nominal source chunks
     int tile = 1;
-    int transport_blocks = 1;  // resident blocks of a transport launch, one a CU
+    int transport_blocks = -1;  // resident blocks of a transport launch, one a CU (-1: not looked up yet)
     int64_t tr_sync = -1;      // steps that went through the transport's slots (-1: not cleared yet)
+    // pinned block of small copies to and from the host, device block of host field
+    // calls (grown on demand, up to kHostBlock and kDevBlock)
+    char *host = nullptr, *dev = nullptr;
+    uint64_t host_bytes = 0, dev_bytes = 0;
     int64_t split_m = -1;  // the cut of the last launch and its target count
     PairSplit split;
     // state
@@ -391,6 +398,7 @@ struct empp_ctx {
     VelRing vel() const { return VelRing{at<double2>(L.vel), cfg.n * (int64_t)cfg.depth}; }
     GuessLine *lines() const { return at<GuessLine>(L.lines); }
     double *T() const { return at<double>(L.T); }
+    double *r() const { return at<double>(L.r); }
     double *u() const { return at<double>(L.u); }
     double *E() const { return at<double>(L.E); }
     double *B() const { return at<double>(L.B); }
@@ -427,11 +435,41 @@ empp_status reset_err(empp_ctx *ctx)
     return EMPP_OK;
 }
 
-empp_status check_err(empp_ctx *ctx)
+// Read-backs and host field calls up to these sizes go through blocks that the
+// context keeps: one copy and one wait, and no allocation, a call.  N = 256: fields
+// 16 us and state 19 (59 and 72 with a copy, a wait or an allocation for each
+// array); 257 targets of 1000 sources 41 us (91); N = 65536, 3 MB, fields 211 us
+// (240), about the rate of the host's copies.
+constexpr uint64_t kHostBlock = (uint64_t)4 << 20, kDevBlock = (uint64_t)64 << 20;
+
+// The context's pinned block of at least `bytes`, or null where a copy is too
+// large for it.  Every user waits for its copies before it returns.
+char *host_block(empp_ctx *ctx, uint64_t bytes)
 {
-    unsigned long long h[2];
-    HIP_TRY(hipMemcpyAsync(h, ctx->err(), sizeof h, hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    if (bytes > kHostBlock)
+        return nullptr;
+    if (bytes > ctx->host_bytes) {
+        if (ctx->host)
+            (void)hipHostFree(ctx->host);
+        ctx->host = nullptr;
+        ctx->host_bytes = 0;
+        uint64_t size = 64 << 10;
+        while (size < bytes)
+            size *= 2;
+        void *p = nullptr;
+        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        ctx->host = (char *)p;
+        ctx->host_bytes = size;
+    }
+    return ctx->host;
+}
+
+// The outcome of the work that error words h tell of.
+empp_status err_status(empp_ctx *ctx, const unsigned long long h[2])
+{
     if (h[1] != 0) {
         long long a = (long long)(h[0] >> 32), j = (long long)(h[0] & 0xffffffffull);
         empp_status st = reset_err(ctx);
@@ -442,6 +480,15 @@ empp_status check_err(empp_ctx *ctx)
                     (h[1] & kErrDiscriminant) ? "negative discriminant" : "coincident particles (eta = 0)", a, j);
     }
     return EMPP_OK;
+}
+
+empp_status check_err(empp_ctx *ctx)
+{
+    unsigned long long own[2], *h = reinterpret_cast<unsigned long long *>(host_block(ctx, sizeof own));
+    h = h ? h : own;
+    HIP_TRY(hipMemcpyAsync(h, ctx->err(), sizeof own, hipMemcpyDeviceToHost, ctx->stream));
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    return err_status(ctx, h);
 }
 
 // Both {eta_min, v_max^2} slots empty, last dt = cfg.dt.
@@ -655,12 +702,6 @@ empp_status empp_create(const empp_config *cfg, empp_ctx **out)
         delete ctx;
         return st;
     }
-    int cus = 0;
-    if (hipError_t e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device); e != hipSuccess) {
-        delete ctx;
-        return fail(EMPP_EDEVICE, "compute units of device %d: %s", cfg->device, hipGetErrorString(e));
-    }
-    ctx->transport_blocks = std::min(cus, kTransportBlocks);
     // set-up of the allocation-free entry point: the address of this
     // device's scratch array (looked up once per device)
     {
@@ -715,6 +756,10 @@ void empp_destroy(empp_ctx *ctx)
                     (void *)ctx->sg.loss_first})
         if (p)
             (void)hipFree(p);
+    if (ctx->host)
+        (void)hipHostFree(ctx->host);
+    if (ctx->dev)
+        (void)hipFree(ctx->dev);
     if (ctx->owns_ws && ctx->ws)
         (void)hipFree(ctx->ws);
     delete ctx;
@@ -1046,49 +1091,92 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
         return fail(EMPP_EINVAL, "NULL argument");
     if (!all_finite(x, 3 * (uint64_t)m))
         return fail(EMPP_EINVAL, "non-finite target position");
-    // an error latched by earlier asynchronous work (a step) is reported
-    // here as that work's, before this call's own pairs can latch one
-    if ((st = check_err(ctx)) != EMPP_OK)
-        return fail(st, "an earlier step: %s", std::string(g_last_error).c_str());
     const int64_t N = ctx->cfg.n;
     if (self_index)
         for (int64_t a = 0; a < m; ++a)
             if (self_index[a] < -1 || self_index[a] >= N)
                 return fail(EMPP_EINVAL, "self_index[%lld] out of range", (long long)a);
-    uint64_t bytes = 3 * m * sizeof(double) * 3 + (self_index ? m * sizeof(int64_t) : 0) +
-                     (kstar ? (uint64_t)m * N * sizeof(int32_t) : 0) + 4 * kAlign;
-    char *tmp = nullptr;
-    hipError_t e = hipMalloc((void **)&tmp, bytes);
-    if (e != hipSuccess)
-        return fail(EMPP_ENOMEM, "hipMalloc(%llu) for fields_at failed", (unsigned long long)bytes);
+    // device block: x, self, E, B, k*; the pinned block holds the same, or as
+    // far as B, then the error words before and after the call's pairs
     uint64_t o = 0;
     auto take = [&](uint64_t b) {
-        char *p = tmp + o;
+        uint64_t at = o;
         o = align_up(o + b);
-        return p;
+        return at;
     };
-    double *xd = (double *)take(3 * m * sizeof(double));
-    double *Ed = (double *)take(3 * m * sizeof(double));
-    double *Bd = (double *)take(3 * m * sizeof(double));
-    int64_t *sd = self_index ? (int64_t *)take(m * sizeof(int64_t)) : nullptr;
-    int32_t *kd = kstar ? (int32_t *)take((uint64_t)m * N * sizeof(int32_t)) : nullptr;
+    const uint64_t xo = take(3 * m * sizeof(double)), so = take(self_index ? m * sizeof(int64_t) : 0);
+    const uint64_t Eo = take(3 * m * sizeof(double)), Bo = take(3 * m * sizeof(double)), fields_end = o;
+    const uint64_t ko = take(kstar ? (uint64_t)m * N * sizeof(int32_t) : 0), bytes = o;
+    char *tmp = nullptr, *dev = ctx->dev;
+    if (bytes > ctx->dev_bytes) {
+        // grown for this and later calls, or for this call alone
+        if (bytes <= kDevBlock && ctx->dev) {
+            HIP_TRY(hipFree(ctx->dev));
+            ctx->dev = nullptr;
+            ctx->dev_bytes = 0;
+        }
+        hipError_t e = hipMalloc((void **)&tmp, bytes);
+        if (e != hipSuccess)
+            return fail(EMPP_ENOMEM, "hipMalloc(%llu) for fields_at failed", (unsigned long long)bytes);
+        dev = tmp;
+        if (bytes <= kDevBlock) {
+            ctx->dev = tmp;
+            ctx->dev_bytes = bytes;
+            tmp = nullptr;
+        }
+    }
+    char *h = host_block(ctx, bytes + 4 * sizeof(unsigned long long));
+    const bool k_host = h && kstar;
+    const uint64_t host_end = h ? bytes : fields_end;
+    if (!h)
+        h = host_block(ctx, host_end + 4 * sizeof(unsigned long long));
+    unsigned long long *words = h ? reinterpret_cast<unsigned long long *>(h + host_end) : nullptr;
+    auto earlier = [](empp_status e) { return fail(e, "an earlier step: %s", std::string(g_last_error).c_str()); };
     auto body = [&]() -> empp_status {
-        HIP_TRY(hipMemcpyAsync(xd, x, 3 * m * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-        if (sd)
-            HIP_TRY(hipMemcpyAsync(sd, self_index, m * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
-        empp_status s2 = fields_dev_impl(ctx, m, xd, sd, Ed, Bd, kd);
+        // an error latched by earlier asynchronous work (a step) is reported
+        // here as that work's: its words are read before this call's own pairs
+        // can latch one
+        if (h) {
+            HIP_TRY(hipMemcpyAsync(words, ctx->err(), 2 * sizeof *words, hipMemcpyDeviceToHost, ctx->stream));
+            std::memcpy(h + xo, x, 3 * m * sizeof(double));
+            if (self_index)
+                std::memcpy(h + so, self_index, m * sizeof(int64_t));
+            HIP_TRY(hipMemcpyAsync(dev, h, Eo, hipMemcpyHostToDevice, ctx->stream));
+        } else {
+            if (empp_status e = check_err(ctx); e != EMPP_OK)
+                return earlier(e);
+            HIP_TRY(hipMemcpyAsync(dev + xo, x, 3 * m * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
+            if (self_index)
+                HIP_TRY(hipMemcpyAsync(dev + so, self_index, m * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
+        }
+        double *Ed = reinterpret_cast<double *>(dev + Eo), *Bd = reinterpret_cast<double *>(dev + Bo);
+        int32_t *kd = kstar ? reinterpret_cast<int32_t *>(dev + ko) : nullptr;
+        empp_status s2 = fields_dev_impl(ctx, m, reinterpret_cast<double *>(dev + xo),
+                                         self_index ? reinterpret_cast<int64_t *>(dev + so) : nullptr, Ed, Bd, kd);
         if (s2 != EMPP_OK)
             return s2;
-        HIP_TRY(hipMemcpyAsync(E, Ed, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-        HIP_TRY(hipMemcpyAsync(B, Bd, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-        if (kd)
-            HIP_TRY(hipMemcpyAsync(kstar, kd, (uint64_t)m * N * sizeof(int32_t), hipMemcpyDeviceToHost,
-                                   ctx->stream));
-        return check_err(ctx);
+        if (kd && !k_host)
+            HIP_TRY(hipMemcpyAsync(kstar, kd, (uint64_t)m * N * sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream));
+        if (!h) {
+            HIP_TRY(hipMemcpyAsync(E, Ed, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+            HIP_TRY(hipMemcpyAsync(B, Bd, 3 * m * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+            return check_err(ctx);
+        }
+        HIP_TRY(hipMemcpyAsync(h + Eo, Ed, host_end - Eo, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipMemcpyAsync(words + 2, ctx->err(), 2 * sizeof *words, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        if (empp_status e = err_status(ctx, words); e != EMPP_OK)
+            return earlier(e);
+        std::memcpy(E, h + Eo, 3 * m * sizeof(double));
+        std::memcpy(B, h + Bo, 3 * m * sizeof(double));
+        if (k_host)
+            std::memcpy(kstar, h + ko, (uint64_t)m * N * sizeof(int32_t));
+        return err_status(ctx, words + 2);
     };
     st = body();
     (void)hipStreamSynchronize(ctx->stream);
-    (void)hipFree(tmp);
+    if (tmp)
+        (void)hipFree(tmp);
     return st;
 }
 
@@ -1108,25 +1196,29 @@ empp_status empp_get_state(empp_ctx *ctx, double *r, double *u, double *t, int64
         return fail(EMPP_EINVAL, "NULL context");
     if (!ctx->have_history)
         return fail(EMPP_ESTATE, "no state yet");
-    empp_status st = empp_sync(ctx);
+    empp_status st = set_device(ctx);
     if (st != EMPP_OK)
         return st;
     const int64_t N = ctx->cfg.n;
-    if (r) {
-        double *tmp = nullptr;
-        HIP_TRY(hipMalloc((void **)&tmp, 3 * N * sizeof(double)));
-        hipError_t e = launch_newest_positions(ctx->present_pos(), tmp, N, ctx->present_depth(), ctx->present_head(),
-                                               ctx->stream);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(r, tmp, 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream);
-        if (e == hipSuccess)
-            e = hipStreamSynchronize(ctx->stream);
-        (void)hipFree(tmp);
-        if (e != hipSuccess)
-            return fail(EMPP_EDEVICE, "get_state: %s", hipGetErrorString(e));
-    }
-    if (u) {
-        HIP_TRY(hipMemcpyAsync(u, ctx->u(), 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+    const uint64_t span = ctx->L.u + 3 * N * sizeof(double) - ctx->L.err;
+    char *h = r && u ? host_block(ctx, span) : nullptr;
+    if (!h && (st = check_err(ctx)) != EMPP_OK)
+        return st;
+    if (r)
+        HIP_TRY(launch_newest_positions(ctx->present_pos(), ctx->r(), N, ctx->present_depth(), ctx->present_head(),
+                                        ctx->stream));
+    if (h) {
+        HIP_TRY(hipMemcpyAsync(h, ctx->err(), span, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        if ((st = err_status(ctx, reinterpret_cast<unsigned long long *>(h))) != EMPP_OK)
+            return st;
+        std::memcpy(r, h + (ctx->L.r - ctx->L.err), 3 * N * sizeof(double));
+        std::memcpy(u, h + (ctx->L.u - ctx->L.err), 3 * N * sizeof(double));
+    } else {
+        if (r)
+            HIP_TRY(hipMemcpyAsync(r, ctx->r(), 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
+        if (u)
+            HIP_TRY(hipMemcpyAsync(u, ctx->u(), 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipStreamSynchronize(ctx->stream));
     }
     if (t)
@@ -1177,10 +1269,22 @@ empp_status empp_get_fields(empp_ctx *ctx, double *E, double *B)
         return fail(EMPP_EINVAL, "NULL argument");
     if (!ctx->have_history)
         return fail(EMPP_ESTATE, "no state yet");
-    empp_status st = empp_sync(ctx);
+    empp_status st = set_device(ctx);
     if (st != EMPP_OK)
         return st;
     const int64_t N = ctx->cfg.n;
+    const uint64_t span = ctx->L.err + 2 * sizeof(unsigned long long) - ctx->L.E;
+    if (char *h = host_block(ctx, span)) {
+        HIP_TRY(hipMemcpyAsync(h, ctx->E(), span, hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+        if ((st = err_status(ctx, reinterpret_cast<unsigned long long *>(h + (ctx->L.err - ctx->L.E)))) != EMPP_OK)
+            return st;
+        std::memcpy(E, h, 3 * N * sizeof(double));
+        std::memcpy(B, h + (ctx->L.B - ctx->L.E), 3 * N * sizeof(double));
+        return EMPP_OK;
+    }
+    if ((st = check_err(ctx)) != EMPP_OK)
+        return st;
     HIP_TRY(hipMemcpyAsync(E, ctx->E(), 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipMemcpyAsync(B, ctx->B(), 3 * N * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -1716,6 +1820,11 @@ empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, i
     // one, 470 in one; 262144: 1736, 657), in blocks of 256, beyond 65536 particles
     // of more (128 blocks of 512 at N = 65536: 506 us).
     int64_t done = 0;
+    if (ctx->transport_blocks < 0) {
+        int cus = 0;
+        HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->cfg.device));
+        ctx->transport_blocks = std::min(cus, kTransportBlocks);
+    }
     int threads = 256;
     while (threads < 1024 && (ctx->cfg.n + threads - 1) / threads > ctx->transport_blocks)
         threads *= 2;
@@ -1737,19 +1846,23 @@ empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, i
         p.step = ctx->tr_step++;
         HIP_TRY(timed(ctx, 1, [&]() { return launch_transport(p, ctx->stream); }));
     }
-    struct {
+    // error words, clock and the word of a wait that gave up
+    struct Words {
+        unsigned long long err[2];
+        char pad[kAlign - 2 * sizeof(unsigned long long)];
         double t;
         unsigned long long fail;
-    } h{};
-    HIP_TRY(hipMemcpyAsync(&h, ctx->stime(), sizeof h, hipMemcpyDeviceToHost, ctx->stream));
+    } own{}, *h = reinterpret_cast<Words *>(host_block(ctx, sizeof own));
+    h = h ? h : &own;
+    HIP_TRY(hipMemcpyAsync(h, ctx->err(), sizeof own, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
-    if (ctx->tr_sync >= 0 && h.fail) {
+    if (ctx->tr_sync >= 0 && h->fail) {
         ctx->tr_sync = -1;
         return fail(EMPP_EDEVICE, "a wait of the transport kernel timed out");
     }
-    ctx->t_now = h.t;
+    ctx->t_now = h->t;
     ctx->step += nsteps;
-    return check_err(ctx);
+    return err_status(ctx, h->err);
 }
 
 // ---- checkpoint --------------------------------------------------------------
