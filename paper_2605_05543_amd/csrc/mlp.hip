@@ -58,17 +58,19 @@ __device__ __forceinline__ unsigned short bf16_bits(float f)
 }
 __device__ __forceinline__ float bf16_value(unsigned short h) { return __uint_as_float((uint32_t)h << 16); }
 
-__device__ __forceinline__ float silu(float x) { return x / (1.0f + __expf(-x)); }
+// Training form: the value, and its derivative from the same exponential.
+__device__ __forceinline__ float silu(float x, float &grad)
+{
+    const float den = 1.0f + __expf(-x);
+    const float s = 1.0f / den;
+    grad = s * (1.0f + x * (1.0f - s));
+    return x / den;
+}
 // Inference form: hardware exp2 and reciprocal (a few ulp of float, far
 // below the bf16 rounding the activations then take).
 __device__ __forceinline__ float silu_fast(float x)
 {
     return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
-}
-__device__ __forceinline__ float silu_grad(float x)
-{
-    float s = 1.0f / (1.0f + __expf(-x));
-    return s * (1.0f + x * (1.0f - s));
 }
 
 // Network weights staged in LDS: W1 [128][16] (K padded, column 10 is 0),
@@ -157,10 +159,10 @@ __device__ __forceinline__ s4 pack4(float a, float b, float c, float d)
 // Forward pass of 16 rows held by one wavefront.  x4: the 4 features
 // 4 (l/16) .. 4 (l/16) + 3 of row l % 16 (zero beyond 10).  Returns z of
 // row l % 16 (valid in every lane).  For training (KEEP) it keeps the
-// pre-activations in registers and writes the bf16 activations H1^T and
+// activations' derivatives in registers and writes the bf16 activations H1^T and
 // H2^T ([unit][row], 16 rows) to the wavefront's LDS tiles.
 struct FwdState {
-    f4 a1[8], a2[8];            // pre-activations (D layout)
+    f4 g1[8], g2[8];            // derivatives of the activations (D layout)
     unsigned short *h1t, *h2t;  // LDS tiles of H1^T, H2^T
 };
 
@@ -179,9 +181,13 @@ __device__ __forceinline__ float net_forward(const NetLds &s, s4 xb, FwdState &s
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float pre = d[r] + s.b1[mt * 16 + 4 * g + r];
-            if (KEEP)
-                st.a1[mt][r] = pre;
-            v[r] = KEEP ? silu(pre) : silu_fast(pre);
+            if constexpr (KEEP) {
+                float grad;
+                v[r] = silu(pre, grad);
+                st.g1[mt][r] = grad;
+            } else {
+                v[r] = silu_fast(pre);
+            }
         }
         h1[mt] = pack4(v[0], v[1], v[2], v[3]);
         if (KEEP) {
@@ -199,16 +205,25 @@ __device__ __forceinline__ float net_forward(const NetLds &s, s4 xb, FwdState &s
             s8 a = lds_s8(&s.W2[(mt * 16 + col) * kW2S + kt * 32 + 8 * g]);
             acc = mfma32(a, cat(h1[2 * kt], h1[2 * kt + 1]), acc);
         }
+        float v[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             int j = mt * 16 + 4 * g + r;
             float pre = acc[r] + s.b2[j];
-            float h = KEEP ? silu(pre) : silu_fast(pre);
-            if (KEEP) {
-                st.a2[mt][r] = pre;
-                st.h2t[j * 16 + col] = bf16_bits(h);
+            if constexpr (KEEP) {
+                float grad;
+                v[r] = silu(pre, grad);
+                st.g2[mt][r] = grad;
+            } else {
+                v[r] = silu_fast(pre);
             }
-            z += s.W3[j] * h;
+            z += s.W3[j] * v[r];
+        }
+        if (KEEP) {
+            const s4 h2 = pack4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                st.h2t[(mt * 16 + 4 * g + r) * 16 + col] = (unsigned short)h2[r];
         }
     };
     if (KEEP) {
@@ -331,6 +346,11 @@ __global__ __launch_bounds__(256) void mlp_forward_kernel(const MlpPacked *net, 
 // summed in a fixed order (FP64, so the result does not depend on
 // scheduling), then Adam (bias-corrected) updates the FP32 master and the
 // packed bf16 copy the next step's forward pass reads.
+// What bounds a step of 8192 rows (34 us; 46 with a counter barrier, the rows,
+// the coefficients and the parameters' state loaded where they are used, and the
+// activations' exponential taken twice): round trips between the XCDs (the
+// network 5 us, the partials' 9 MB out and back 10, two barriers 5) and about
+// 10 us of activations and products on one wavefront a SIMD.
 struct TrainLds {
     NetLds net;
     alignas(16) unsigned short W2T[kHid * kW2S];  // W2 transposed (columns in slot order)
@@ -352,10 +372,34 @@ __device__ __forceinline__ void store_shared(T &dst, T val)
     __hip_atomic_store(&dst, val, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The same of four floats at byte offset `at` of a buffer (its device-scope bit
+// is 16; an atomic store has 8 bytes at most).
+__device__ __forceinline__ void store_shared4(__amdgpu_buffer_rsrc_t buf, int at, f4 v)
+{
+    typedef unsigned int u4v __attribute__((ext_vector_type(4)));
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4v, v), buf, at, 0, 16);
+}
+
+// A lane's row of a chunk of 64: features and target (zero beyond n).
+struct TrainRow {
+    float f[kIn], y;
+};
+__device__ __forceinline__ void load_row(TrainRow &t, const float *X, const float *y, int64_t chunk, int64_t n)
+{
+    const int64_t row = chunk + (threadIdx.x >> 6) * 16 + (threadIdx.x & 15);
+#pragma unroll
+    for (int k = 0; k < kIn; ++k)
+        t.f[k] = row < n ? X[row * kIn + k] : 0.0f;
+    t.y = row < n ? y[row] : 0.0f;
+}
+
 // Phase 1 for this block's rows X[n][10], y[n] (64 per chunk, chunks
-// strided by the grid): the block's partial gradient into out.
-__device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X, const float *y, int64_t n,
-                               float scale, float *out)
+// strided by the grid, the first one's in `t`): the block's partial gradient
+// into out.  The products of the weight gradients take the layer's inputs as
+// the first operand, so that a lane's four results are neighbours in the flat
+// layout: one 16-byte store in place of four.
+__device__ void block_gradient(TrainLds &s, const MlpPacked *net, TrainRow &t, const float *X, const float *y,
+                               int64_t n, float scale, float *out)
 {
     load_net(s.net, net);
     load_matrix(s.W2T, net->W2T);
@@ -377,15 +421,14 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X
     for (int64_t chunk = (int64_t)blockIdx.x * 64; chunk < n; chunk += (int64_t)gridDim.x * 64) {
         const int64_t row = chunk + w * 16 + col;
         const bool live = row < n;
-        float f[kIn];
-#pragma unroll
-        for (int k = 0; k < kIn; ++k)
-            f[k] = live ? X[row * kIn + k] : 0.0f;
+        if (chunk != (int64_t)blockIdx.x * 64)
+            load_row(t, X, y, chunk, n);
+        const float *f = t.f;
         FwdState st;
         st.h1t = s.H1T[w];
         st.h2t = s.H2T[w];
         float z = net_forward<true>(s.net, feature_operand(f), st);
-        float res = live ? z - y[row] : 0.0f;
+        float res = live ? z - t.y : 0.0f;
         float dz = live ? scale * res : 0.0f;
         if (l < 16)
             sqsum += res * res;
@@ -398,7 +441,7 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 int j = mt * 16 + 4 * g + r;
-                v[r] = s.net.W3[j] * dz * silu_grad(st.a2[mt][r]);
+                v[r] = s.net.W3[j] * dz * st.g2[mt][r];
             }
             da2[mt] = pack4(v[0], v[1], v[2], v[3]);
 #pragma unroll
@@ -415,11 +458,11 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X
                 s8 a = lds_s8(&s.W2T[(mt * 16 + col) * kW2S + kt * 32 + 8 * g]);
                 acc = mfma32(a, cat(da2[2 * kt], da2[2 * kt + 1]), acc);
             }
+            const s4 da1 = pack4(acc[0] * st.g1[mt][0], acc[1] * st.g1[mt][1], acc[2] * st.g1[mt][2],
+                                 acc[3] * st.g1[mt][3]);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                int j = mt * 16 + 4 * g + r;
-                s.dA1T[w][j * 16 + col] = bf16_bits(acc[r] * silu_grad(st.a1[mt][r]));
-            }
+            for (int r = 0; r < 4; ++r)
+                s.dA1T[w][(mt * 16 + 4 * g + r) * 16 + col] = (unsigned short)da1[r];
         }
         // [X | 1]^T and [dz | 0]^T of this wave's 16 rows
         for (int k = 4 * g; k < 4 * g + 4; ++k) {
@@ -437,44 +480,47 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
                 const int mt = 2 * w + a;
-                // A: dA2^T rows j, K = rows i;  B: [H1 | 1] rows i, N = units k
+                // A: [H1 | 1]^T units k, K = rows i;  B: dA2 rows i, N = units j
                 const int ra = (mt * 16 + col) * 16 + 4 * g;
                 s8 A2 = cat(lds_s4(&s.dA2T[w0][ra]), lds_s4(&s.dA2T[w1][ra]));
 #pragma unroll
                 for (int nt = 0; nt < 8; ++nt) {
                     const int rb = (nt * 16 + col) * 16 + 4 * g;
-                    gW2[a][nt] = mfma32(A2, cat(lds_s4(&s.H1T[w0][rb]), lds_s4(&s.H1T[w1][rb])), gW2[a][nt]);
+                    gW2[a][nt] = mfma32(cat(lds_s4(&s.H1T[w0][rb]), lds_s4(&s.H1T[w1][rb])), A2, gW2[a][nt]);
                 }
-                // ones column (bias gradient): B[i][k] = 1 for k = 0
+                // ones row (bias gradient): A[k][i] = 1 for k = 0
                 const s4 one4 = (col == 0) ? pack4(1.0f, 1.0f, 1.0f, 1.0f) : s4{0, 0, 0, 0};
-                gW2[a][8] = mfma32(A2, cat(one4, one4), gW2[a][8]);
+                gW2[a][8] = mfma32(cat(one4, one4), A2, gW2[a][8]);
                 s8 A1 = cat(lds_s4(&s.dA1T[w0][ra]), lds_s4(&s.dA1T[w1][ra]));
                 const int rx = col * 16 + 4 * g;
-                gW1[a] = mfma32(A1, cat(lds_s4(&s.XeT[w0][rx]), lds_s4(&s.XeT[w1][rx])), gW1[a]);
+                gW1[a] = mfma32(cat(lds_s4(&s.XeT[w0][rx]), lds_s4(&s.XeT[w1][rx])), A1, gW1[a]);
                 s8 H2 = cat(lds_s4(&s.H2T[w0][ra]), lds_s4(&s.H2T[w1][ra]));
-                gW3[a] = mfma32(H2, cat(lds_s4(&s.dzT[w0][rx]), lds_s4(&s.dzT[w1][rx])), gW3[a]);
+                gW3[a] = mfma32(cat(lds_s4(&s.dzT[w0][rx]), lds_s4(&s.dzT[w1][rx])), H2, gW3[a]);
             }
         }
         __syncthreads();
     }
-    // this block's partial gradient in the flat layout
+    // this block's partial gradient in the flat layout: a lane holds units
+    // k = 16 nt + 4 g + r of row j
+    const __amdgpu_buffer_rsrc_t buf =
+        __builtin_amdgcn_make_buffer_rsrc(out, 0, kPartStride * (int)sizeof(float), 0x00027000);
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-        const int mt = 2 * w + a;
+        const int j = (2 * w + a) * 16 + col;
+#pragma unroll
+        for (int nt = 0; nt < 8; ++nt)
+            store_shared4(buf, (kOffW2 + j * kHid + nt * 16 + 4 * g) * (int)sizeof(float), gW2[a][nt]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int j = mt * 16 + 4 * g + r;
-#pragma unroll
-            for (int nt = 0; nt < 8; ++nt)
-                store_shared(out[kOffW2 + j * kHid + nt * 16 + col], gW2[a][nt][r]);
-            if (col == 0)
-                store_shared(out[kOffB2 + j], gW2[a][8][r]);
-            if (col < kIn)
-                store_shared(out[kOffW1 + j * kIn + col], gW1[a][r]);
-            if (col == kIn)
+            const int k = 4 * g + r;
+            if (k < kIn)
+                store_shared(out[kOffW1 + j * kIn + k], gW1[a][r]);
+            if (k == kIn)
                 store_shared(out[kOffB1 + j], gW1[a][r]);
-            if (col == 0)
-                store_shared(out[kOffW3 + j], gW3[a][r]);
+        }
+        if (g == 0) {
+            store_shared(out[kOffB2 + j], gW2[a][8][0]);
+            store_shared(out[kOffW3 + j], gW3[a][0]);
         }
     }
     // b3 and the squared residuals: wave sums, then the block's
@@ -494,41 +540,41 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, const float *X
     }
 }
 
-// Grid-wide barrier of a cooperative launch.  sync[0] counts arrivals;
-// the block that brings it to the target writes the target into every
-// block's flag (sync[kSyncLine (b + 1)], one 128-byte line per block), and
-// each other block waits on its own flag, so no line is polled by more than
-// one block.  Thread 0 of a block carries the block's synchronisation: its
-// arrival releases what the block wrote (the block's threads have finished
-// their stores at the preceding __syncthreads) and acquires what the blocks
-// before it released; the flags are polled with relaxed loads and one
-// acquire fence follows the wait, so the XCD's L2 is invalidated once per
-// barrier, not once per poll.  The wait is bounded (about a second); a block
-// that gives up sets *fail, which the host reports, and goes on, so every
-// wave still ends.
+// Grid-wide barrier number `epoch` of a cooperative launch: every block stores
+// the number into its slot and its first wavefront waits for all the others',
+// one hop (a counter, its last arrival and a flag per block are three).  Every wavefront has waited for its
+// own stores before the block's first __syncthreads; thread 0 then releases
+// what the block wrote, and one acquire follows the wait, so the XCD's L2 is
+// invalidated once per barrier and block, not once per poll.  The block spends
+// the wait in `meanwhile`.  The wait is bounded (about a
+// second); a block that gives up sets *fail, which the host reports, and goes
+// on, so every wave still ends.
 constexpr unsigned kSyncSpinLimit = 1u << 20;
-__device__ void grid_barrier(unsigned long long *sync, unsigned long long target, unsigned int *fail)
+template <typename F>
+__device__ __forceinline__ void grid_barrier(unsigned long long *sync, unsigned long long epoch, unsigned int *fail,
+                                             F &&meanwhile)
 {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned long long seen =
-            __hip_atomic_fetch_add(sync, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1;
-        if (seen == target) {
+    if (threadIdx.x < 64) {
+        if (threadIdx.x == 0) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            for (int b = 0; b < (int)gridDim.x; ++b)
-                __hip_atomic_store(&sync[kSyncLine * (b + 1)], target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        } else {
-            unsigned long long *flag = &sync[kSyncLine * (blockIdx.x + 1)];
-            unsigned spins = 0;
-            while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+            __hip_atomic_store(&sync[blockIdx.x], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        meanwhile();
+        unsigned spins = 0;
+        for (int b = threadIdx.x; b < (int)gridDim.x; b += 64) {
+            while (__hip_atomic_load(&sync[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
                 if (++spins > kSyncSpinLimit) {
                     atomicOr(fail, 1u);
                     break;
                 }
-                __builtin_amdgcn_s_sleep(2);
+                __builtin_amdgcn_s_sleep(1);
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    } else {
+        meanwhile();
     }
     __syncthreads();
 }
@@ -554,69 +600,92 @@ __device__ __forceinline__ void pack_param(MlpPacked *net, int q, float x)
     }
 }
 
+// Learning rate and Adam's bias corrections of a step.
+struct AdamCoef {
+    float lr, c1, c2;
+};
+constexpr float kBeta1 = 0.9f, kBeta2 = 0.999f;
+__device__ __forceinline__ AdamCoef adam_coef(const TrainRun &p, int64_t gs, int it)
+{
+    const double frac = p.total > 1 ? (double)gs / (double)(p.total - 1) : 1.0;
+    const float step = (float)(p.adam0 + it + 1);
+    AdamCoef a;
+    a.lr = (float)(p.lr_final + 0.5 * (p.lr - p.lr_final) * (1.0 + cos(M_PI * frac)));
+    a.c1 = 1.0f - powf(kBeta1, step);
+    a.c2 = 1.0f - powf(kBeta2, step);
+    return a;
+}
+
 // Phase 2 for this block's slice [q0, q1) of the parameters (q0 a
 // multiple of 4): column c of the slice's 16-byte units is summed over the
 // block partials b = r, r + R, ... by thread (c, r), in FP64, and the R
-// sums of a column are then added in order r = 0, 1, ...: a fixed order,
-// whatever the scheduling.  Then the gradient, Adam (bias-corrected) on
-// the FP32 masters and the packed network for those parameters.
-__device__ void reduce_and_update(const TrainRun &p, double4 *red, int q0, int q1, int64_t gs, int it)
+// sums of a parameter are then added in order r = 0, 1, ... by its thread: a
+// fixed order, whatever the scheduling.  Then the gradient, Adam
+// (bias-corrected) on the FP32 masters and the packed network for those
+// parameters.  A thread's partials are loaded together (20 in flight: all of
+// 128 blocks' for a slice of 144) behind the parameter's own state: 11.4 us of a
+// step with 8 in flight, four parameters a thread and the state loaded at the
+// end, 4.5 now.
+__device__ void reduce_and_update(const TrainRun &p, const AdamCoef &ac, double4 *red, int q0, int q1, int64_t gs)
 {
-    const int nb = (int)gridDim.x;
-    const double frac = p.total > 1 ? (double)gs / (double)(p.total - 1) : 1.0;
-    const float lr = (float)(p.lr_final + 0.5 * (p.lr - p.lr_final) * (1.0 + cos(M_PI * frac)));
-    const float step = (float)(p.adam0 + it + 1);
-    const float beta1 = 0.9f, beta2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.0f - powf(beta1, step), c2 = 1.0f - powf(beta2, step);
+    constexpr int kAhead = 20;
+    const int nb = __builtin_amdgcn_readfirstlane(p.row_blocks);
+    const float eps = 1e-8f;
     const int ncol = (q1 - q0 + 3) / 4;
     const int cols = ncol < 64 ? ncol : 64;  // columns per pass
     const int R = kMlpThreads / cols;         // partial subsets per column
     const int c = threadIdx.x % cols, r = threadIdx.x / cols;
     for (int c0 = 0; c0 < ncol; c0 += cols) {
         const int col = c0 + c;
+        // this thread's parameter
+        const int q = q0 + 4 * c0 + (int)threadIdx.x;
+        const bool mine = (int)threadIdx.x < 4 * cols && q < q1, update = mine && p.apply && q < kParams;
+        float m0 = 0.0f, v0 = 0.0f, x0 = 0.0f;
+        if (update) {
+            m0 = p.m[q];
+            v0 = p.v[q];
+            x0 = p.master[q];
+        }
         double4 acc = make_double4(0.0, 0.0, 0.0, 0.0);
         if (r < R && col < ncol) {
             const float4 *src = reinterpret_cast<const float4 *>(p.part + q0) + col;
-#pragma unroll 8
-            for (int b = r; b < nb; b += R) {
-                const float4 x = src[(int64_t)b * (kPartStride / 4)];
-                acc.x += x.x;
-                acc.y += x.y;
-                acc.z += x.z;
-                acc.w += x.w;
+            for (int b0 = r; b0 < nb; b0 += kAhead * R) {
+                float4 x[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k)
+                    if (b0 + k * R < nb)
+                        x[k] = src[(int64_t)(b0 + k * R) * (kPartStride / 4)];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) {
+                    if (b0 + k * R < nb) {
+                        acc.x += x[k].x;
+                        acc.y += x[k].y;
+                        acc.z += x[k].z;
+                        acc.w += x[k].w;
+                    }
+                }
             }
         }
         if (r < R)
             red[r * cols + c] = acc;
         __syncthreads();
-        if (r == 0 && col < ncol) {
-            double4 t = red[c];
-            for (int k = 1; k < R; ++k) {
-                const double4 u = red[k * cols + c];
-                t.x += u.x;
-                t.y += u.y;
-                t.z += u.z;
-                t.w += u.w;
-            }
-            const double tv[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int q = q0 + 4 * col + e;
-                if (q >= q1)
-                    break;
-                const float gr = (float)tv[e];
-                p.grad[q] = gr;
-                if (q == kParams && gs == 0)
-                    *p.loss_first = gr;
-                if (p.apply && q < kParams) {
-                    const float mm = beta1 * p.m[q] + (1.0f - beta1) * gr;
-                    const float vv = beta2 * p.v[q] + (1.0f - beta2) * gr * gr;
-                    p.m[q] = mm;
-                    p.v[q] = vv;
-                    const float x = p.master[q] - lr * (mm / c1) / (sqrtf(vv / c2) + eps);
-                    p.master[q] = x;
-                    pack_param(p.net, q, x);
-                }
+        if (mine) {
+            const double *sums = reinterpret_cast<const double *>(red) + threadIdx.x;
+            double tv = sums[0];
+            for (int k = 1; k < R; ++k)
+                tv += sums[4 * k * cols];
+            const float gr = (float)tv;
+            p.grad[q] = gr;
+            if (q == kParams && gs == 0)
+                *p.loss_first = gr;
+            if (update) {
+                const float mm = kBeta1 * m0 + (1.0f - kBeta1) * gr;
+                const float vv = kBeta2 * v0 + (1.0f - kBeta2) * gr * gr;
+                p.m[q] = mm;
+                p.v[q] = vv;
+                const float x = x0 - ac.lr * (mm / ac.c1) / (sqrtf(vv / ac.c2) + eps);
+                p.master[q] = x;
+                pack_param(p.net, q, x);
             }
         }
         __syncthreads();
@@ -630,11 +699,17 @@ __device__ void reduce_and_update(const TrainRun &p, double4 *red, int q0, int q
 // packed network.
 __global__ __launch_bounds__(kMlpThreads) void mlp_train_kernel(const TrainRun *run)
 {
-    // The run's parameters are read from device memory where they are used
-    // (the empty asm statements below mark memory as changed, so they are
-    // not held in registers across the step loop, which would spill).
-    const TrainRun &p = *run;
-    extern __shared__ unsigned char tls_raw[];
+    // The run's parameters are read from LDS where they are used (the empty asm
+    // statements below mark memory as changed, so they are not held in registers
+    // across the step loop, which would spill).
+    __shared__ TrainRun p;
+    __shared__ AdamCoef ac;
+    for (int k = threadIdx.x; k < (int)(sizeof(TrainRun) / sizeof(uint32_t)); k += kMlpThreads)
+        reinterpret_cast<uint32_t *>(&p)[k] = reinterpret_cast<const uint32_t *>(run)[k];
+    __syncthreads();
+    // (aligned here: behind the static variables its 16-byte reads may straddle,
+    // 4 us a step)
+    extern __shared__ __attribute__((aligned(16))) unsigned char tls_raw[];
     TrainLds &s = *reinterpret_cast<TrainLds *>(tls_raw);
     // phase 2's column sums reuse the H1^T tiles (16 KiB, 512 double4)
     static_assert(sizeof(s.H1T) >= kMlpThreads * sizeof(double4), "phase-2 sums fit the H1^T tiles");
@@ -643,33 +718,46 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_train_kernel(const TrainRun *
     const int slice = ((kParams + 1 + nb - 1) / nb + 3) & ~3;
     const int q0 = min((int)blockIdx.x * slice, kParams + 1);
     const int q1 = min(q0 + slice, kParams + 1);
-    unsigned long long target = p.sync_base;
+    unsigned long long epoch = p.sync_base;
+    // first row of step gs's batch
+    auto batch_start = [](int64_t gs) {
+        const int64_t start = (gs * p.batch) % p.count;
+        return start + p.batch > p.count ? (int64_t)0 : start;
+    };
+    // a step's rows are loaded while the step before it ends
+    TrainRow row;
+    int64_t start = batch_start(p.step0);
+    load_row(row, p.X + start * kIn, p.y + start, (int64_t)blockIdx.x * 64, p.batch);
     for (int it = 0; it < p.steps; ++it) {
         asm volatile("" ::: "memory");
         const int64_t gs = p.step0 + it;
-        int64_t start = (gs * p.batch) % p.count;
-        if (start + p.batch > p.count)
-            start = 0;
-        block_gradient(s, p.net, p.X + start * kIn, p.y + start, p.batch, 2.0f / (float)p.batch,
+        block_gradient(s, p.net, row, p.X + start * kIn, p.y + start, p.batch, 2.0f / (float)p.batch,
                        p.part + (int64_t)blockIdx.x * kPartStride);
-        target += nb;
-        grid_barrier(p.sync, target, p.fail);
+        grid_barrier(p.sync, ++epoch, p.fail, [&]() {
+            if (threadIdx.x >= kMlpThreads - 64) {
+                const AdamCoef a = adam_coef(p, gs, it);
+                if (threadIdx.x == kMlpThreads - 1)
+                    ac = a;
+            }
+        });
         asm volatile("" ::: "memory");
         if (q0 < q1)
-            reduce_and_update(p, red, q0, q1, gs, it);
+            reduce_and_update(p, ac, red, q0, q1, gs);
         if (it + 1 < p.steps) {
-            target += nb;
-            grid_barrier(p.sync, target, p.fail);
+            grid_barrier(p.sync, ++epoch, p.fail, [&]() {
+                start = batch_start(gs + 1);
+                load_row(row, p.X + start * kIn, p.y + start, (int64_t)blockIdx.x * 64, p.batch);
+            });
         }
     }
 }
 
-// Clears the barrier counter, the flags of up to kSyncMaxBlocks blocks and
-// the failure word (one block of kMlpThreads threads).
+// Clears the slots of up to kSyncMaxBlocks blocks and the failure word (one
+// block of kMlpThreads threads).
 __global__ void mlp_sync_clear_kernel(unsigned long long *sync, unsigned int *fail)
 {
-    for (int i = threadIdx.x; i < kSyncLine * (kSyncMaxBlocks + 1); i += blockDim.x)
-        sync[i] = 0;
+    for (int k = threadIdx.x; k < kSyncMaxBlocks; k += kMlpThreads)
+        sync[k] = 0;
     if (threadIdx.x == 0)
         *fail = 0;
 }
@@ -943,9 +1031,9 @@ hipError_t launch_mlp_sync_clear(unsigned long long *sync, unsigned int *fail, h
 }
 
 // run->steps optimizer steps (or, with apply = 0, one gradient evaluation)
-// on nblocks resident blocks; run is in device memory; *run->sync must hold
-// run->sync_base arrivals when the launch starts, and holds sync_base +
-// nblocks (2 steps - 1) after it.
+// on nblocks resident blocks; run is in device memory; the slots of run->sync
+// must hold run->sync_base when the launch starts, and hold sync_base +
+// 2 steps - 1 after it.
 hipError_t launch_mlp_train(const TrainRun *run, int nblocks, hipStream_t s)
 {
     const TrainRun *arg = run;

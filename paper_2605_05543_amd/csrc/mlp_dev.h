@@ -19,10 +19,8 @@ constexpr int kOffB2 = kOffW2 + kHid * kHid;
 constexpr int kOffW3 = kOffB2 + kHid;
 constexpr int kOffB3 = kOffW3 + kHid;
 constexpr int kParams = kOffB3 + 1;  // 18049
-// blocks of a training launch at most; its barrier buffer holds the
-// arrival counter and one flag per block, each in a line of kSyncLine u64
+// blocks of a training launch at most; its barrier buffer has a slot for each
 constexpr int kSyncMaxBlocks = 512;
-constexpr int kSyncLine = 16;
 // a block's partial gradient: kParams values and its sum of squared
 // residuals, padded to whole 16-byte units
 constexpr int kPartStride = (kParams + 1 + 3) & ~3;
@@ -67,16 +65,17 @@ struct TrainRun {
     int64_t count;     // rows available
     int32_t batch;     // rows per optimizer step
     int32_t steps;     // optimizer steps of this launch
+    int32_t row_blocks;  // blocks with rows (the others only share phase 2)
     int64_t step0;     // index of the launch's first step within the run
     int64_t total;     // steps of the run (learning-rate schedule)
     int64_t adam0;     // Adam steps taken before this launch
     double lr, lr_final;
     int32_t apply;     // 0: one gradient evaluation, no update
-    float *part;       // [gridDim.x][kPartStride]
+    float *part;       // [row_blocks][kPartStride]
     float *grad;       // [kParams + 1]: summed gradient, then the sum of squared residuals
     float *master, *m, *v;
     float *loss_first; // the run's first sum of squared residuals
-    unsigned long long *sync;  // barrier counter and per-block flags
+    unsigned long long *sync;  // [kSyncMaxBlocks] the last barrier each block came to
     unsigned long long sync_base;
     unsigned int *fail;  // set when a barrier wait gives up
 };
