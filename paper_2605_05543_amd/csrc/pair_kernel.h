@@ -703,10 +703,13 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         acc[3] = __builtin_fma(-h.z, E.y, __builtin_fma(h.y, E.z, acc[3]));
                         acc[4] = __builtin_fma(-h.x, E.z, __builtin_fma(h.z, E.x, acc[4]));
                         acc[5] = __builtin_fma(-h.y, E.x, __builtin_fma(h.x, E.y, acc[5]));
-                        if (ADAPT && en >= p.eta_allow) {
+                        if constexpr (ADAPT) {
+                            // selects, no branch (N = 65536: 30.6 ms, 31.7 with one)
+                            const bool in = en >= p.eta_allow;
                             const double dx = vt.x - vr.x, dy = vt.y - vr.y, dz = vt.z - vr.z;
-                            eta_min = fmin(eta_min, en);
-                            dv2_max = fmax(dv2_max, dx * dx + dy * dy + dz * dz);
+                            const double d2 = dx * dx + dy * dy + dz * dz;
+                            eta_min = in & (en < eta_min) ? en : eta_min;
+                            dv2_max = in & (d2 > dv2_max) ? d2 : dv2_max;
                         }
                     }
                 }
