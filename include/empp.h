@@ -37,7 +37,10 @@
  * (target, source), by the next call that synchronises: empp_sync,
  * empp_get_state, empp_get_history, empp_get_fields, empp_get_diag,
  * empp_step_until_switch, empp_handoff, empp_transport and empp_fields_at
- * (which reports an error left by an earlier step before its own launch).
+ * (which reports an error left by an earlier step as that step's).  Small
+ * read-backs and host field calls go through a pinned block of up to 4 MiB (up
+ * to four are kept for later contexts) and a device block of up to 64 MiB that
+ * the context keeps.
  *
  * Threading: a context is bound to one device and must not be used by two
  * threads at once.  Different contexts are independent.
@@ -79,7 +82,10 @@ typedef enum {
 
 typedef enum {
     EMPP_GUESS_BISECT = 0,    /* the paper's search: oldest-sample test, then
-                                 bisection of the whole history            */
+                                 bisection of the whole history.  A pass that
+                                 neither counts nor writes k* tries the bracket
+                                 on the chord to the oldest sample first (the
+                                 same bracket: its two samples decide)      */
     EMPP_GUESS_MLP = 1,       /* start from the surrogate network's delay
                                  (modes 1 and 3 need depth >= 5: the
                                  network reads the slot 4 steps back;
@@ -112,7 +118,8 @@ typedef struct {
     int32_t precision;     /* empp_precision                                 */
     int32_t guess;         /* empp_guess                                     */
     int32_t device;        /* HIP device ordinal                             */
-    int32_t source_splits; /* 0: automatic; else number of source chunks     */
+    int32_t source_splits; /* 0: chosen for each launch from its targets, N
+                              and depth; else number of source chunks       */
     void *stream;          /* hipStream_t or NULL                            */
     void *workspace;       /* caller-owned device memory, or NULL            */
     uint64_t workspace_bytes;
@@ -150,7 +157,8 @@ typedef struct {
 typedef struct {
     uint64_t pairs;        /* (target, source) pairs evaluated               */
     uint64_t before;       /* pairs whose retarded time precedes the history */
-    uint64_t probes;       /* light-cone sign tests performed                */
+    uint64_t probes;       /* light-cone sign tests of the mode's plain search
+                              (the one a counting pass runs)                */
     uint64_t rescues;      /* FP32 roots recomputed in FP64 (mixed precision) */
     uint64_t fallbacks;    /* guided searches that fell back to bisection    */
 } empp_counters;
@@ -222,7 +230,7 @@ empp_status empp_fields_at_dev(empp_ctx *ctx, double t, int64_t m, const double 
  * array the library holds on every GPU it runs on until the process ends
  * (its address is looked up once per device by empp_create), so at most
  * floor(128 MiB / (96 B x source chunks)) targets fit one call (10922 with
- * the 128 chunks of N = 65536): EINVAL beyond that.  Guess modes
+ * the 128 nominal chunks of N = 65536): EINVAL beyond that.  Guess modes
  * EMPP_GUESS_MLP and EMPP_GUESS_MLP_PAIR are EUNSUPPORTED here.  Results
  * are bit-identical to empp_fields_at_dev's (same chunks, same merge
  * order).  All calls on one GPU share the array, which keeps the last
@@ -353,8 +361,10 @@ empp_status empp_handoff(empp_ctx *ctx);
  *   dt = min(dt_max, gyro_fraction * 2 pi m / |q| * min_i gamma_i / |B(y_i)|),
  * a fraction of the shortest gyro-period in the bunch, re-evaluated on the
  * device before every step (dt_max when nothing sees a field).  Blocks
- * until done and advances the context's time.  ESTATE before the handoff;
- * EINVAL on dt_max <= 0, gyro_fraction <= 0 or nsteps < 0.               */
+ * until done and advances the context's time.  Five or more steps of up to
+ * 262144 particles run in one cooperative launch (EDEVICE if a wait of that
+ * launch timed out).  ESTATE before the handoff; EINVAL on dt_max <= 0,
+ * gyro_fraction <= 0 or nsteps < 0.                                       */
 empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, int64_t nsteps);
 
 /* Checkpoint: write the whole state (history ring in Stage I, or the

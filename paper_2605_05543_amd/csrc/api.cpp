@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -98,7 +99,7 @@ constexpr uint64_t kAlign = 256;
 uint64_t align_up(uint64_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    uint64_t ring_w, vel, lines, T, r, u, E, B, part, err, counters, diag, order, pos, skey, st, tslots, ad, kc, kc_bytes, total;
+    uint64_t ring_w, vel, lines, T, r, u, E, B, part, err, counters, diag, order, pos, skey, st, tslots, ad, host, kc, kc_bytes, total;
 };
 
 
@@ -248,6 +249,14 @@ PairSplit pair_split(const empp_config &c, int64_t m)
     return s;
 }
 
+// Read-backs and host field calls up to these sizes go through blocks that the
+// context keeps (the device's smaller ones in the workspace): one copy and one
+// wait, and no allocation, a call.  N = 256: fields 16 us and state 19 (59 and 72
+// with a copy, a wait or an allocation for each array); 257 targets of 1000
+// sources 41 us (91); N = 65536, 3 MB, fields 211 us (240), about the rate of the
+// host's copies.
+constexpr uint64_t kHostBlock = (uint64_t)4 << 20, kDevBlock = (uint64_t)64 << 20;
+
 Layout layout_for(const empp_config &c)
 {
     Layout L{};
@@ -283,6 +292,7 @@ Layout layout_for(const empp_config &c)
     // previous-step brackets (warm start): uint16 per (source, target)
     L.kc_bytes = c.guess == EMPP_GUESS_PREVIOUS ? N * N * sizeof(uint16_t) : 0;
     L.kc = L.kc_bytes ? take(L.kc_bytes) : 0;
+    L.host = take(kHostBlock);  // host field calls
     L.total = o;
     return L;
 }
@@ -342,6 +352,14 @@ bool all_finite(const double *a, uint64_t n)
 
 }  // namespace
 
+namespace {
+// A pinned block (see host_block).
+struct HostBlock {
+    char *p = nullptr;
+    uint64_t bytes = 0;
+};
+}  // namespace
+
 struct empp_ctx {
     empp_config cfg{};
     Layout L{};
@@ -353,10 +371,11 @@ struct empp_ctx {
     int tile = 1;
     int transport_blocks = -1;  // resident blocks of a transport launch, one a CU (-1: not looked up yet)
     int64_t tr_sync = -1;      // steps that went through the transport's slots (-1: not cleared yet)
-    // pinned block of small copies to and from the host, device block of host field
-    // calls (grown on demand, up to kHostBlock and kDevBlock)
-    char *host = nullptr, *dev = nullptr;
-    uint64_t host_bytes = 0, dev_bytes = 0;
+    // pinned block of small copies to and from the host, device block of larger host
+    // field calls (grown on demand, up to kDevBlock)
+    HostBlock host;
+    char *dev = nullptr;
+    uint64_t dev_bytes = 0;
     int64_t split_m = -1;  // the cut of the last launch and its target count
     PairSplit split;
     // state
@@ -435,36 +454,58 @@ empp_status reset_err(empp_ctx *ctx)
     return EMPP_OK;
 }
 
-// Read-backs and host field calls up to these sizes go through blocks that the
-// context keeps: one copy and one wait, and no allocation, a call.  N = 256: fields
-// 16 us and state 19 (59 and 72 with a copy, a wait or an allocation for each
-// array); 257 targets of 1000 sources 41 us (91); N = 65536, 3 MB, fields 211 us
-// (240), about the rate of the host's copies.
-constexpr uint64_t kHostBlock = (uint64_t)4 << 20, kDevBlock = (uint64_t)64 << 20;
+// Pinned blocks that contexts gave back, for the next one (pinning one takes 50
+// (64 KiB) to 500 us (4 MiB)): at most four, under a lock.
+constexpr int kSpareBlocks = 4;
+std::mutex g_spare_lock;
+HostBlock g_spare[kSpareBlocks];
 
-// The context's pinned block of at least `bytes`, or null where a copy is too
-// large for it.  Every user waits for its copies before it returns.
+// Takes a block back from a context whose stream has been waited for.
+void give_back_host_block(HostBlock block)
+{
+    if (!block.p)
+        return;
+    {
+        std::lock_guard<std::mutex> hold(g_spare_lock);
+        for (HostBlock &b : g_spare)
+            if (!b.p) {
+                b = block;
+                return;
+            }
+    }
+    (void)hipHostFree(block.p);
+}
+
+// The context's pinned block of at least `bytes`, or null where they are too
+// many for it.  Every user waits for its copies before it returns.
 char *host_block(empp_ctx *ctx, uint64_t bytes)
 {
     if (bytes > kHostBlock)
         return nullptr;
-    if (bytes > ctx->host_bytes) {
-        if (ctx->host)
-            (void)hipHostFree(ctx->host);
-        ctx->host = nullptr;
-        ctx->host_bytes = 0;
-        uint64_t size = 64 << 10;
-        while (size < bytes)
-            size *= 2;
-        void *p = nullptr;
-        if (hipHostMalloc(&p, size, hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            return nullptr;
-        }
-        ctx->host = (char *)p;
-        ctx->host_bytes = size;
+    if (bytes <= ctx->host.bytes)
+        return ctx->host.p;
+    give_back_host_block(ctx->host);
+    ctx->host = HostBlock{};
+    {
+        std::lock_guard<std::mutex> hold(g_spare_lock);
+        for (HostBlock &b : g_spare)
+            if (b.bytes >= bytes) {
+                ctx->host = b;
+                b = HostBlock{};
+                return ctx->host.p;
+            }
     }
-    return ctx->host;
+    uint64_t size = 64 << 10;
+    while (size < bytes)
+        size *= 2;
+    void *p = nullptr;
+    if (hipHostMalloc(&p, size, hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    ctx->host.p = (char *)p;
+    ctx->host.bytes = size;
+    return ctx->host.p;
 }
 
 // The outcome of the work that error words h tell of.
@@ -484,8 +525,7 @@ empp_status err_status(empp_ctx *ctx, const unsigned long long h[2])
 
 empp_status check_err(empp_ctx *ctx)
 {
-    unsigned long long own[2], *h = reinterpret_cast<unsigned long long *>(host_block(ctx, sizeof own));
-    h = h ? h : own;
+    unsigned long long own[2], *h = ctx->host.p ? reinterpret_cast<unsigned long long *>(ctx->host.p) : own;
     HIP_TRY(hipMemcpyAsync(h, ctx->err(), sizeof own, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return err_status(ctx, h);
@@ -756,8 +796,7 @@ void empp_destroy(empp_ctx *ctx)
                     (void *)ctx->sg.loss_first})
         if (p)
             (void)hipFree(p);
-    if (ctx->host)
-        (void)hipHostFree(ctx->host);
+    give_back_host_block(ctx->host);
     if (ctx->dev)
         (void)hipFree(ctx->dev);
     if (ctx->owns_ws && ctx->ws)
@@ -1107,8 +1146,8 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
     const uint64_t xo = take(3 * m * sizeof(double)), so = take(self_index ? m * sizeof(int64_t) : 0);
     const uint64_t Eo = take(3 * m * sizeof(double)), Bo = take(3 * m * sizeof(double)), fields_end = o;
     const uint64_t ko = take(kstar ? (uint64_t)m * N * sizeof(int32_t) : 0), bytes = o;
-    char *tmp = nullptr, *dev = ctx->dev;
-    if (bytes > ctx->dev_bytes) {
+    char *tmp = nullptr, *dev = bytes <= kHostBlock ? ctx->at<char>(ctx->L.host) : ctx->dev;
+    if (bytes > kHostBlock && bytes > ctx->dev_bytes) {
         // grown for this and later calls, or for this call alone
         if (bytes <= kDevBlock && ctx->dev) {
             HIP_TRY(hipFree(ctx->dev));
