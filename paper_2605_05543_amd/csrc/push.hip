@@ -497,9 +497,10 @@ __global__ void transport_kernel(TransportParams p)
 // Step minima of a transport_steps_kernel launch: thread b < gridDim.x waits for
 // block b's minimum of the step that `tag` (the sign bit, else clear in these
 // positive doubles) and `slots` (even or odd steps) name; returns the smallest
-// to every thread.  The wait is bounded (about a second): a thread that gives up
-// sets *fail, the block then returns a negative value and ends its launch.
-constexpr unsigned kTransportSpinLimit = 1u << 20;
+// to every thread.  The wait is bounded (some 15 s: a block may have to wait for
+// another stream's pair pass to leave its CU): a thread that gives up sets *fail,
+// the block then returns a negative value and ends its launch.
+constexpr unsigned kTransportSpinLimit = 1u << 24;
 __device__ inline double wait_for_minima(const unsigned long long *slots, unsigned long long tag,
                                          unsigned long long *fail, double (*wmin)[4])
 {

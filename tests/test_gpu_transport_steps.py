@@ -39,3 +39,48 @@ def test_transport_steps_together(n, field, tmp_path):
             out.append((*[np.array(x) for x in res], f.read_bytes() if f.exists() else b""))
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+def test_transport_beside_other_streams():
+    """Three threads on streams of their own, two transporting and one
+    stepping and reading back: each ends where it ends alone."""
+    import threading
+
+    import torch
+
+    from paper_2605_05543_amd._lib import Context
+
+    print("case transport beside other streams", flush=True)
+    n = 2048
+    rng = np.random.default_rng(5)
+    r = 1e-3 * rng.standard_normal((3, n))
+    r[0] += 3 * RE
+    u = 3e8 * (0.1 * rng.standard_normal((3, n)) + np.array([[0.0], [1.0], [1.5]]))
+
+    def run(kind, out, i):
+        with torch.cuda.stream(torch.cuda.Stream()), Context(n=n, depth=16, q=Q, m=ME, dt=1e-13, ext_field=1,
+                                                             dipole_b0=B0, dipole_re=RE) as ctx:
+            ctx.init_bunch(r, u, 0.0)
+            ctx.init_history_straight()
+            if kind == "step":
+                for _ in range(20):
+                    ctx.step(1)
+                    E, B = ctx.fields()
+                out[i] = (E, B, *ctx.state()[:2])
+            else:
+                ctx.handoff()
+                for _ in range(10):
+                    ctx.transport(1e-7, 1 / 32, 30)
+                out[i] = ctx.state()[:3]
+
+    kinds = ["transport", "step", "transport"]
+    alone, beside = [None] * 3, [None] * 3
+    for i, k in enumerate(kinds):
+        run(k, alone, i)
+    threads = [threading.Thread(target=run, args=(k, beside, i)) for i, k in enumerate(kinds)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    for a, b in zip(alone, beside):
+        assert b is not None and all(np.array_equal(x, y) for x, y in zip(a, b))
