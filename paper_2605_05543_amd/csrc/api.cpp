@@ -197,15 +197,18 @@ struct PairSplit {
 // chunks are, so that results do not depend on them: chunks are multiples of
 // the nominal one, or its halves of whole runs of 8, and a target has one
 // wavefront.
-PairSplit pair_split(const empp_config &c, int64_t m)
+//
+// `nominal` chunks and `held` rows (of N targets) are those of the context's
+// layout: they depend on the search mode it was created with, and a launch after a
+// change of mode writes the same partials.
+PairSplit pair_split(const empp_config &c, int nominal, int held, int64_t m)
 {
-    const int nominal = splits_for(c);
     const int64_t N = c.n, base = (N + nominal - 1) / nominal;
     m = std::min(m, N);  // a larger call runs N targets at a time
     const bool mixed = c.precision == EMPP_MIXED;
     const int64_t ts = pair_fp64_tile(c.depth), waves = (m + 63) / 64;
     // what the partials hold, here and in the allocation-free call
-    const int64_t room = std::min((int64_t)part_rows(c) * N, std::max((int64_t)nominal * m, (int64_t)1 << 20));
+    const int64_t room = std::min((int64_t)held * N, std::max((int64_t)nominal * m, (int64_t)1 << 20));
     const int64_t most = std::max<int64_t>(1, std::min(room / m, (int64_t)kMaxSplits));
     PairSplit s;
     double best = INFINITY;
@@ -367,7 +370,7 @@ struct empp_ctx {
     char *ws = nullptr;
     bool owns_ws = false;
     void *scratch = nullptr;  // this device's copy of the allocation-free entry point's scratch
-    int nsplit = 1;  // nominal source chunks
+    int nsplit = 1, part_rows = 1;  // nominal source chunks and rows of partials of the layout
     int tile = 1;
     int transport_blocks = -1;  // resident blocks of a transport launch, one a CU (-1: not looked up yet)
     int64_t tr_sync = -1;      // steps that went through the transport's slots (-1: not cleared yet)
@@ -546,7 +549,7 @@ PairParams pair_params(empp_ctx *ctx, int64_t m)
 {
     PairParams p{};
     if (ctx->split_m != m) {
-        ctx->split = pair_split(ctx->cfg, m);
+        ctx->split = pair_split(ctx->cfg, ctx->nsplit, ctx->part_rows, m);
         ctx->split_m = m;
     }
     const PairSplit sp = ctx->split;
@@ -679,6 +682,9 @@ hipError_t launch_guesses(empp_ctx *ctx, PairParams &p, float *G_pair = nullptr,
     });
 }
 
+// Whether `bytes` of memory hold the launch's partials, [nsplit][12][m].
+bool part_fits(const PairParams &p, uint64_t bytes) { return (uint64_t)p.nsplit * 12 * (uint64_t)p.m * sizeof(double) <= bytes; }
+
 // The guess data the launch's search mode starts from: the chord's for a
 // bisection (a cold warm start's too), else the newest velocity's.
 void set_guess_line(empp_ctx *ctx, PairParams &p)
@@ -690,6 +696,8 @@ void set_guess_line(empp_ctx *ctx, PairParams &p)
 hipError_t launch_pair(empp_ctx *ctx, PairParams &p, bool kstar, float *G_pair = nullptr,
                        double3 *cent_pair = nullptr)
 {
+    if (!part_fits(p, (uint64_t)ctx->part_rows * 12 * (uint64_t)ctx->cfg.n * sizeof(double)))
+        return hipErrorInvalidValue;
     set_guess_line(ctx, p);
     hipError_t eg = launch_guesses(ctx, p, G_pair, cent_pair);
     if (eg != hipSuccess)
@@ -736,6 +744,7 @@ empp_status empp_create(const empp_config *cfg, empp_ctx **out)
     ctx->cfg = *cfg;
     ctx->L = layout_for(*cfg);
     ctx->nsplit = splits_for(*cfg);
+    ctx->part_rows = part_rows(*cfg);
     ctx->tile = pair_fp64_tile(cfg->depth);
     ctx->stream = (hipStream_t)cfg->stream;
     if ((st = set_device(ctx)) != EMPP_OK) {
@@ -1106,6 +1115,8 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
         p.self_index = self_dev ? self_dev + a0 : nullptr;
         p.kstar = kstar_dev ? kstar_dev + a0 * N : nullptr;
         p.part = reinterpret_cast<double *>(ctx->scratch);
+        if (!part_fits(p, noalloc_scratch_bytes()))
+            return fail(EMPP_EINVAL, "%d source chunks of %lld targets exceed the scratch array", p.nsplit, (long long)mc);
         // launched directly: no timing events, no guess buffers
         set_guess_line(ctx, p);
         hipError_t e = ctx->cfg.precision == EMPP_MIXED
@@ -2110,6 +2121,27 @@ empp_status empp_load(empp_ctx *ctx, const char *path)
     ctx->tr_step = h.tr_step;
     ctx->t_now = h.t_now;
     ctx->t_origin = h.t_origin;
+    return EMPP_OK;
+}
+
+// Not part of the ABI: the cut of a launch of m targets on a context created
+// with `created` and switched to (precision, guess), on the host alone.  out:
+// chunks, sources of a chunk, log2 of a target's wavefronts, rows of N targets the
+// partials hold, nominal chunks, most targets of an allocation-free call.
+empp_status empp_internal_launch_cut(const empp_config *created, int32_t precision, int32_t guess, int64_t m,
+                                     int64_t out[6])
+{
+    empp_status st = validate(created);
+    if (st != EMPP_OK)
+        return st;
+    empp_config now = *created;
+    now.precision = precision;
+    now.guess = guess;
+    const int nominal = splits_for(*created), held = part_rows(*created);
+    const PairSplit s = pair_split(now, nominal, held, m);
+    const int64_t v[6] = {s.nsplit, s.src, s.sg_log2, held, nominal,
+                          (int64_t)(noalloc_scratch_bytes() / ((uint64_t)nominal * 12 * sizeof(double)))};
+    std::copy(v, v + 6, out);
     return EMPP_OK;
 }
 
