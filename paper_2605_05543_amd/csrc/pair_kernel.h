@@ -615,6 +615,9 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         }
                     } else {
                         --bisect_left;
+                        // the search below gives every lane a bracket, also
+                        // where all are left out (a single target's own source)
+                        miss = true;
                     }
                     if (any_lane(miss)) {
                         // The paper's search: the oldest sample, then the
