@@ -363,7 +363,7 @@ empp_status empp_handoff(empp_ctx *ctx);
  * device before every step (dt_max when nothing sees a field).  Blocks
  * until done and advances the context's time.  Five or more steps of up to
  * 262144 particles run in one cooperative launch (EDEVICE if a wait of that
- * launch timed out).  ESTATE before the handoff; EINVAL on dt_max <= 0,
+ * launch timed out; the context then holds no state).  ESTATE before the handoff; EINVAL on dt_max <= 0,
  * gyro_fraction <= 0 or nsteps < 0.                                       */
 empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, int64_t nsteps);
 

@@ -373,6 +373,7 @@ struct empp_ctx {
     int nsplit = 1, part_rows = 1;  // nominal source chunks and rows of partials of the layout
     int tile = 1;
     int transport_blocks = -1;  // resident blocks of a transport launch, one a CU (-1: not looked up yet)
+    unsigned wait_polls = kWaitPolls;  // a wait between the blocks of a cooperative launch gives up after
     int64_t tr_sync = -1;      // steps that went through the transport's slots (-1: not cleared yet)
     // pinned block of small copies to and from the host, device block of larger host
     // field calls (grown on demand, up to kDevBlock)
@@ -1870,6 +1871,7 @@ empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, i
     p.t = ctx->stime();
     p.slots = ctx->tslots();
     p.fail = reinterpret_cast<unsigned long long *>(ctx->stime() + 1);
+    p.polls = ctx->wait_polls;
     // Several steps go into one launch while every particle has a thread of its
     // own on resident blocks, one a CU (N = 65536: 100 steps 725 us in launches of
     // one, 470 in one; 262144: 1736, 657), in blocks of 256, beyond 65536 particles
@@ -1912,8 +1914,11 @@ empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, i
     HIP_TRY(hipMemcpyAsync(h, ctx->err(), sizeof own, hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     if (ctx->tr_sync >= 0 && h->fail) {
+        // the particles are at different times: nothing valid remains
         ctx->tr_sync = -1;
-        return fail(EMPP_EDEVICE, "a wait of the transport kernel timed out");
+        ctx->have_history = false;
+        ctx->handed_off = false;
+        return fail(EMPP_EDEVICE, "a wait of the transport kernel timed out; the context holds no state");
     }
     ctx->t_now = h->t;
     ctx->step += nsteps;
@@ -2123,6 +2128,10 @@ empp_status empp_load(empp_ctx *ctx, const char *path)
     ctx->t_origin = h.t_origin;
     return EMPP_OK;
 }
+
+// Not part of the ABI: polls after which this context's waits between the blocks
+// of a cooperative launch give up (0: at the first that finds no value).
+void empp_internal_wait_polls(empp_ctx *ctx, uint32_t polls) { ctx->wait_polls = polls; }
 
 // Not part of the ABI: the cut of a launch of m targets on a context created
 // with `created` and switched to (precision, guess), on the host alone.  out:

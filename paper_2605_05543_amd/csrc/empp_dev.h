@@ -239,8 +239,12 @@ struct TransportParams {
     unsigned long long *slots;
     int64_t nsteps, sync_step;
     unsigned long long *fail;
+    unsigned polls;  // a wait gives up after
 };
 constexpr int kTransportBlocks = 256;
+// Polls after which a wait between the blocks of a cooperative launch gives up,
+// some 15 s: a block may have to wait for another stream's pair pass to leave its CU.
+constexpr unsigned kWaitPolls = 1u << 24;
 
 constexpr unsigned long long kPosInfBits = 0x7FF0000000000000ull;
 

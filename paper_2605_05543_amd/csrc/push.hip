@@ -497,25 +497,26 @@ __global__ void transport_kernel(TransportParams p)
 // Step minima of a transport_steps_kernel launch: thread b < gridDim.x waits for
 // block b's minimum of the step that `tag` (the sign bit, else clear in these
 // positive doubles) and `slots` (even or odd steps) name; returns the smallest
-// to every thread.  The wait is bounded (some 15 s: a block may have to wait for
-// another stream's pair pass to leave its CU): a thread that gives up sets *fail,
-// the block then returns a negative value and ends its launch.
-constexpr unsigned kTransportSpinLimit = 1u << 24;
+// to every thread.  The wait is bounded: a thread that has polled `polls` times, or
+// sees that another gave up, sets *fail, and the block gets a negative value.
 __device__ inline double wait_for_minima(const unsigned long long *slots, unsigned long long tag,
-                                         unsigned long long *fail, double (*wmin)[4])
+                                         unsigned long long *fail, unsigned polls, double (*wmin)[4])
 {
     double v = __longlong_as_double((long long)kPosInfBits);
     if (threadIdx.x < gridDim.x) {
         unsigned long long x;
         unsigned spins = 0;
+        bool lost = false;
         while (((x = __hip_atomic_load(&slots[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 63) != tag) {
-            if (++spins > kTransportSpinLimit) {
+            lost = ++spins > polls || ((spins & 255) == 0 &&
+                                       __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
+            if (lost) {
                 atomicOr(fail, 1ull);
                 break;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        v = spins > kTransportSpinLimit ? -1.0 : __longlong_as_double((long long)(x & ~(1ull << 63)));
+        v = lost ? -1.0 : __longlong_as_double((long long)(x & ~(1ull << 63)));
     }
     const int w = threadIdx.x >> 6;
     if (w < kTransportBlocks / 64) {
@@ -542,10 +543,13 @@ __device__ inline double wait_for_minima(const unsigned long long *slots, unsign
 // read every block's previous minimum) overwrites none that is still read.
 // 4.3 us a step at N = 65536, 6.2 at 262144 (of which about 2.4 are the chain; polls
 // without a pause between them 0.5 more).  The launch is cooperative, so every
-// block is resident.
+// block is resident.  A block whose wait gives up ends and writes nothing, and so
+// does every block of a launch queued behind; the bunch then has no valid state.
 __global__ __launch_bounds__(1024) void transport_steps_kernel(TransportParams p)
 {
     __shared__ double wblock[2][16], wall[2][4];
+    if (__syncthreads_or(__hip_atomic_load(p.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+        return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = i < p.N, first = i == 0;
     const double inf = __longlong_as_double((long long)kPosInfBits);
@@ -597,9 +601,9 @@ __global__ __launch_bounds__(1024) void transport_steps_kernel(TransportParams p
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         kold = kmin;
-        kmin = wait_for_minima(slots, tag, p.fail, &wall[par]);
+        kmin = wait_for_minima(slots, tag, p.fail, p.polls, &wall[par]);
         if (kmin < 0.0)
-            break;
+            return;
     }
     if (live) {
         p.pos[i] = y;
