@@ -1894,6 +1894,7 @@ empp_status empp_transport(empp_ctx *ctx, double dt_max, double gyro_fraction, i
         p.step = ctx->tr_step;
         p.sync_step = ctx->tr_sync;
         p.nsteps = std::min<int64_t>(nsteps - done, 4096);
+        p.queued = done > 0;
         HIP_TRY(timed(ctx, 1, [&]() { return launch_transport_steps(p, threads, ctx->stream); }));
         ctx->tr_step += p.nsteps;
         ctx->tr_sync += p.nsteps;

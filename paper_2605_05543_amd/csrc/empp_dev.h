@@ -240,6 +240,7 @@ struct TransportParams {
     int64_t nsteps, sync_step;
     unsigned long long *fail;
     unsigned polls;  // a wait gives up after
+    int32_t queued;  // behind another launch of the call, which may have given up
 };
 constexpr int kTransportBlocks = 256;
 // Polls after which a wait between the blocks of a cooperative launch gives up,

@@ -548,7 +548,7 @@ __device__ inline double wait_for_minima(const unsigned long long *slots, unsign
 __global__ __launch_bounds__(1024) void transport_steps_kernel(TransportParams p)
 {
     __shared__ double wblock[2][16], wall[2][4];
-    if (__syncthreads_or(__hip_atomic_load(p.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+    if (p.queued && __syncthreads_or(__hip_atomic_load(p.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
         return;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool live = i < p.N, first = i == 0;
