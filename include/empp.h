@@ -326,7 +326,8 @@ empp_status empp_surrogate_loss_grad(empp_ctx *ctx, const float *X, const float 
  * partials, Adam, the packed bf16 copy) runs inside one cooperative launch
  * that takes up to 256 steps; results do not depend on scheduling.
  * Synchronous.  EMPP_EDEVICE if a grid-wide barrier of that launch timed
- * out (the parameters are then not to be trusted).                      */
+ * out; the context then holds no network (ESTATE until
+ * empp_surrogate_set).                                                  */
 empp_status empp_surrogate_train(empp_ctx *ctx, const float *X_dev, const float *y_dev, int64_t count,
                                  const empp_train_cfg *cfg, empp_train_report *out);
 

@@ -1680,6 +1680,7 @@ static empp_status surrogate_run(empp_ctx *ctx, const float *X, const float *y, 
         r.sync = ctx->sg.sync;
         r.sync_base = barriers;
         r.fail = ctx->sg.sync_fail;
+        r.polls = ctx->wait_polls;
         barriers += (unsigned long long)(2 * r.steps - 1);
     }
     TrainRun *dev = nullptr;
@@ -1692,8 +1693,12 @@ static empp_status surrogate_run(empp_ctx *ctx, const float *X, const float *y, 
         HIP_TRY(hipStreamSynchronize(ctx->stream));
         unsigned int f = 0;
         HIP_TRY(hipMemcpy(&f, ctx->sg.sync_fail, sizeof(f), hipMemcpyDeviceToHost));
-        if (f)
-            return fail(EMPP_EDEVICE, "a grid barrier of the training kernel timed out");
+        if (f) {
+            // an update that some blocks made and others did not: no network remains
+            ctx->sg.ready = ctx->sg.ready && !apply;
+            return fail(EMPP_EDEVICE, "a grid barrier of the training kernel timed out%s",
+                        apply ? "; the context holds no network" : "");
+        }
         return EMPP_OK;
     };
     empp_status st = body();

@@ -546,13 +546,12 @@ __device__ void block_gradient(TrainLds &s, const MlpPacked *net, TrainRow &t, c
 // own stores before the block's first __syncthreads; thread 0 then releases
 // what the block wrote, and one acquire follows the wait, so the XCD's L2 is
 // invalidated once per barrier and block, not once per poll.  The block spends
-// the wait in `meanwhile`.  The wait is bounded (about a
-// second); a block that gives up sets *fail, which the host reports, and goes
-// on, so every wave still ends.
-constexpr unsigned kSyncSpinLimit = 1u << 20;
+// the wait in `meanwhile`.  The wait is bounded: a block that has polled `polls`
+// times, or sees that another gave up, sets *fail, which the host reports, and
+// `lost` (in LDS, clear before), and gets false; it then ends, so every wave still ends.
 template <typename F>
-__device__ __forceinline__ void grid_barrier(unsigned long long *sync, unsigned long long epoch, unsigned int *fail,
-                                             F &&meanwhile)
+__device__ __forceinline__ bool grid_barrier(unsigned long long *sync, unsigned long long epoch, unsigned int *fail,
+                                             unsigned polls, int &lost, F &&meanwhile)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
@@ -565,8 +564,10 @@ __device__ __forceinline__ void grid_barrier(unsigned long long *sync, unsigned 
         unsigned spins = 0;
         for (int b = threadIdx.x; b < (int)gridDim.x; b += 64) {
             while (__hip_atomic_load(&sync[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
-                if (++spins > kSyncSpinLimit) {
+                if (++spins > polls || ((spins & 255) == 0 &&
+                                        __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
                     atomicOr(fail, 1u);
+                    lost = 1;
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
@@ -577,6 +578,7 @@ __device__ __forceinline__ void grid_barrier(unsigned long long *sync, unsigned 
         meanwhile();
     }
     __syncthreads();
+    return lost == 0;
 }
 
 // One parameter of the packed network from its FP32 master value.
@@ -704,9 +706,15 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_train_kernel(const TrainRun *
     // across the step loop, which would spill).
     __shared__ TrainRun p;
     __shared__ AdamCoef ac;
+    __shared__ int lost;
+    if (threadIdx.x == 0)
+        lost = 0;
     for (int k = threadIdx.x; k < (int)(sizeof(TrainRun) / sizeof(uint32_t)); k += kMlpThreads)
         reinterpret_cast<uint32_t *>(&p)[k] = reinterpret_cast<const uint32_t *>(run)[k];
     __syncthreads();
+    // (an earlier launch of the run gave up)
+    if (p.step0 > 0 && __syncthreads_or(__hip_atomic_load(p.fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+        return;
     // (aligned here: behind the static variables its 16-byte reads may straddle,
     // 4 us a step)
     extern __shared__ __attribute__((aligned(16))) unsigned char tls_raw[];
@@ -733,21 +741,24 @@ __global__ __launch_bounds__(kMlpThreads) void mlp_train_kernel(const TrainRun *
         const int64_t gs = p.step0 + it;
         block_gradient(s, p.net, row, p.X + start * kIn, p.y + start, p.batch, 2.0f / (float)p.batch,
                        p.part + (int64_t)blockIdx.x * kPartStride);
-        grid_barrier(p.sync, ++epoch, p.fail, [&]() {
+        const bool met = grid_barrier(p.sync, ++epoch, p.fail, p.polls, lost, [&]() {
             if (threadIdx.x >= kMlpThreads - 64) {
                 const AdamCoef a = adam_coef(p, gs, it);
                 if (threadIdx.x == kMlpThreads - 1)
                     ac = a;
             }
         });
+        if (!met)
+            return;
         asm volatile("" ::: "memory");
         if (q0 < q1)
             reduce_and_update(p, ac, red, q0, q1, gs);
         if (it + 1 < p.steps) {
-            grid_barrier(p.sync, ++epoch, p.fail, [&]() {
-                start = batch_start(gs + 1);
-                load_row(row, p.X + start * kIn, p.y + start, (int64_t)blockIdx.x * 64, p.batch);
-            });
+            if (!grid_barrier(p.sync, ++epoch, p.fail, p.polls, lost, [&]() {
+                    start = batch_start(gs + 1);
+                    load_row(row, p.X + start * kIn, p.y + start, (int64_t)blockIdx.x * 64, p.batch);
+                }))
+                return;
         }
     }
 }

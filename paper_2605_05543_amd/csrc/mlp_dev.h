@@ -78,6 +78,7 @@ struct TrainRun {
     unsigned long long *sync;  // [kSyncMaxBlocks] the last barrier each block came to
     unsigned long long sync_base;
     unsigned int *fail;  // set when a barrier wait gives up
+    unsigned int polls;  // it gives up after
 };
 
 struct SampleParams {
