@@ -320,7 +320,9 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             rx = p.x[a];
             ry = p.x[p.x_stride + a];
             rz = p.x[2 * p.x_stride + a];
-            self = p.self_index ? (int32_t)p.self_index[a] : -1;
+            // (an index that names no source leaves none out)
+            const int64_t out = p.self_index ? p.self_index[a] : -1;
+            self = out >= 0 && out < p.n_src ? (int32_t)out : -1;
         } else {
             const int64_t tgt = p.order ? (int64_t)p.order[a] : a;
             double4 w = p.ring_w[tgt * D + p.head];
