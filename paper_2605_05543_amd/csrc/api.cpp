@@ -1040,6 +1040,7 @@ static empp_status fields_dev_impl(empp_ctx *ctx, int64_t m, const double *x_dev
         PairParams p = pair_params(ctx, mc);
         p.x = x_dev + a0;
         p.x_stride = m;
+        p.a_base = a0;
         p.self_index = self_dev ? self_dev + a0 : nullptr;
         p.kstar = kstar_dev ? kstar_dev + a0 * N : nullptr;
         float *G_pair = nullptr;
@@ -1113,6 +1114,7 @@ empp_status empp_fields_at_dev_noalloc(empp_ctx *ctx, double t, int64_t m, const
         PairParams p = pair_params(ctx, mc);
         p.x = x_dev + a0;
         p.x_stride = m;
+        p.a_base = a0;
         p.self_index = self_dev ? self_dev + a0 : nullptr;
         p.kstar = kstar_dev ? kstar_dev + a0 * N : nullptr;
         p.part = reinterpret_cast<double *>(ctx->scratch);

@@ -122,6 +122,7 @@ struct PairParams {
     const double *x;
     int64_t x_stride;
     const int64_t *self_index;  // external mode only, may be null
+    int64_t a_base;             // the launch's first target in its call (errors name the call's)
     const int32_t *order;       // step mode: target slot -> particle (spatial order), may be null
     int64_t m;
     int64_t src_per_split;

@@ -799,7 +799,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             }
         }
         if (fail_j != INT32_MAX)
-            report_error(p.err, !p.x && p.order ? (int64_t)p.order[a] : a, fail_j, kErrCoincident);
+            report_error(p.err, !p.x && p.order ? (int64_t)p.order[a] : p.a_base + a, fail_j, kErrCoincident);
     }
     if (ADAPT) {
         // one atomic pair per wavefront

@@ -30,3 +30,18 @@ def test_self_index_beyond_the_sources(fn, precision):
         for base in (1 << 32, -(1 << 32), 1 << 40, 40):
             got = _fields(fn, ctx, T[-1], x, base + np.arange(70) % 40)
             assert all(np.array_equal(a, b) for a, b in zip(ref, got)), base
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("fn", CALLS)
+def test_errors_name_the_calls_target(fn, precision):
+    print(f"case error in a later part of a call precision={precision}", flush=True)
+    n = 40
+    ctx, T, w = _context(n, 16, precision)
+    with ctx:
+        for at in ((3,), (n + 5,), (2 * n + 1, 3 * n - 1)):
+            x = 1.5e-3 * np.random.default_rng(1).standard_normal((3, 3 * n))
+            x[:, at] = w[-1][:, 7:8]  # on a source that is not left out
+            with pytest.raises(_lib.EmppError, match=f"target {at[0]}, source 7") as ei:
+                _fields(fn, ctx, T[-1], x, np.full(3 * n, -1))
+            assert ei.value.status == _lib.EMPP_ENUMERIC
