@@ -1145,10 +1145,16 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
     if (!all_finite(x, 3 * (uint64_t)m))
         return fail(EMPP_EINVAL, "non-finite target position");
     const int64_t N = ctx->cfg.n;
+    // an error latched by earlier asynchronous work (a step) is reported as that
+    // work's, before anything else of the call is looked at or written
+    auto earlier = [](empp_status e) { return fail(e, "an earlier step: %s", std::string(g_last_error).c_str()); };
     if (self_index)
         for (int64_t a = 0; a < m; ++a)
-            if (self_index[a] < -1 || self_index[a] >= N)
+            if (self_index[a] < -1 || self_index[a] >= N) {
+                if ((st = check_err(ctx)) != EMPP_OK)
+                    return earlier(st);
                 return fail(EMPP_EINVAL, "self_index[%lld] out of range", (long long)a);
+            }
     // device block: x, self, E, B, k*; the pinned block holds the same, or as
     // far as B, then the error words before and after the call's pairs
     uint64_t o = 0;
@@ -1160,6 +1166,18 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
     const uint64_t xo = take(3 * m * sizeof(double)), so = take(self_index ? m * sizeof(int64_t) : 0);
     const uint64_t Eo = take(3 * m * sizeof(double)), Bo = take(3 * m * sizeof(double)), fields_end = o;
     const uint64_t ko = take(kstar ? (uint64_t)m * N * sizeof(int32_t) : 0), bytes = o;
+    char *h = host_block(ctx, bytes + 4 * sizeof(unsigned long long));
+    const bool k_host = h && kstar;
+    // where every output comes through the pinned block the earlier work's error
+    // words are copied ahead of the call's own pairs and looked at after the one
+    // wait; nothing else may be left by a call that reports them
+    const bool late = h && !ctx->counting && !ctx->timing;
+    if (!late && (st = check_err(ctx)) != EMPP_OK)
+        return earlier(st);
+    const uint64_t host_end = h ? bytes : fields_end;
+    if (!h)
+        h = host_block(ctx, host_end + 4 * sizeof(unsigned long long));
+    unsigned long long *words = h ? reinterpret_cast<unsigned long long *>(h + host_end) : nullptr;
     char *tmp = nullptr, *dev = bytes <= kHostBlock ? ctx->at<char>(ctx->L.host) : ctx->dev;
     if (bytes > kHostBlock && bytes > ctx->dev_bytes) {
         // grown for this and later calls, or for this call alone
@@ -1178,26 +1196,15 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
             tmp = nullptr;
         }
     }
-    char *h = host_block(ctx, bytes + 4 * sizeof(unsigned long long));
-    const bool k_host = h && kstar;
-    const uint64_t host_end = h ? bytes : fields_end;
-    if (!h)
-        h = host_block(ctx, host_end + 4 * sizeof(unsigned long long));
-    unsigned long long *words = h ? reinterpret_cast<unsigned long long *>(h + host_end) : nullptr;
-    auto earlier = [](empp_status e) { return fail(e, "an earlier step: %s", std::string(g_last_error).c_str()); };
     auto body = [&]() -> empp_status {
-        // an error latched by earlier asynchronous work (a step) is reported
-        // here as that work's: its words are read before this call's own pairs
-        // can latch one
-        if (h) {
+        if (late)
             HIP_TRY(hipMemcpyAsync(words, ctx->err(), 2 * sizeof *words, hipMemcpyDeviceToHost, ctx->stream));
+        if (h) {
             std::memcpy(h + xo, x, 3 * m * sizeof(double));
             if (self_index)
                 std::memcpy(h + so, self_index, m * sizeof(int64_t));
             HIP_TRY(hipMemcpyAsync(dev, h, Eo, hipMemcpyHostToDevice, ctx->stream));
         } else {
-            if (empp_status e = check_err(ctx); e != EMPP_OK)
-                return earlier(e);
             HIP_TRY(hipMemcpyAsync(dev + xo, x, 3 * m * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
             if (self_index)
                 HIP_TRY(hipMemcpyAsync(dev + so, self_index, m * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream));
@@ -1218,8 +1225,9 @@ empp_status empp_fields_at(empp_ctx *ctx, double t, int64_t m, const double *x, 
         HIP_TRY(hipMemcpyAsync(h + Eo, Ed, host_end - Eo, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipMemcpyAsync(words + 2, ctx->err(), 2 * sizeof *words, hipMemcpyDeviceToHost, ctx->stream));
         HIP_TRY(hipStreamSynchronize(ctx->stream));
-        if (empp_status e = err_status(ctx, words); e != EMPP_OK)
-            return earlier(e);
+        if (late)
+            if (empp_status e = err_status(ctx, words); e != EMPP_OK)
+                return earlier(e);
         std::memcpy(E, h + Eo, 3 * m * sizeof(double));
         std::memcpy(B, h + Bo, 3 * m * sizeof(double));
         if (k_host)
