@@ -554,12 +554,13 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                     q1 = value_at(addr(g - 1) + (uint32_t)sizeof(double2), d1);
                 };
                 const bool other = j != self;
+                int n_tests = 0, n_fall = 0;  // of a plain search
                 if constexpr (COUNT || (kChord && KSTAR)) {
                     // The mode's search in its plain form, whose sign tests
                     // are counted: the paper's bisection (the halvings of the
                     // whole history), or a guess confirmed by two samples and
                     // followed by a gallop.
-                    int n = 0, fb = 0, b;
+                    int n = 0, b;
                     if constexpr (kChord) {
                         b = search_bisect(test, D, n);
                         n = b < 0 ? 1 : 1 + (D > 2 ? 32 - __clz(D - 2) : 0);
@@ -575,12 +576,9 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                             n = was_before || k == 1 ? 1 : 2;
                         }
                         if (!hit && other)
-                            b = search_guided(test, D, guess_of(), 6, n, fb);
+                            b = search_guided(test, D, guess_of(), 6, n, n_fall);
                     }
-                    if (COUNT && other) {
-                        probes += n;
-                        nfall += fb;
-                    }
+                    n_tests = n;
                     before = b < 0;
                     bracket_at(before ? D - 1 : b);
                 } else {
@@ -733,6 +731,8 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                 if (COUNT && valid) {
                     npairs += 1;
                     nbefore += before ? 1 : 0;
+                    probes += n_tests;
+                    nfall += n_fall;
                 }
             }
             // plain partial sums over kPlainRun sources, then one compensated
