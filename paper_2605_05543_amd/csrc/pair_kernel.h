@@ -280,8 +280,12 @@ __device__ __forceinline__ bool lw_pair_mixed(double L1d, MixedPair q, bool befo
 __device__ __forceinline__ bool any_lane(bool pred) { return __builtin_amdgcn_ballot_w64(pred) != 0; }
 
 // A wavefront that misses its guess in kMissRun sources in a row bisects the
-// next kBisectRun sources before it guesses again.
-constexpr int kMissRun = 3, kBisectRun = 30;
+// next kBisectRun sources before it guesses again, and twice as many each time
+// that guess misses too, up to kBisectMost (a curving history, N = 65536, D = 512,
+// pair kernel: 35.6 ms with runs of 30, 35.0 so, 34.9 from 62 to 248; N = 16384 with
+// one length, 30, 62 and 126: steps of 2.48, 2.46 and 2.45).  A warm start, whose
+// guesses miss only now and then, keeps to the short run (36.0 ms, 36.5).
+constexpr int kMissRun = 3, kBisectRun = 30, kBisectMost = 240;
 
 // DB: double-buffered tiles (D <= kHalfRecs).
 template <bool MIX, bool KSTAR, bool COUNT, int GUESS, bool ADAPT, bool MID, bool DB>
@@ -306,7 +310,11 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     pair_block_coords(nbx, p.nsplit, bxi, split);
     const int64_t a0 = (int64_t)bxi * targets + tw * 64;
     const int64_t a = a0 + lane;
-    const bool active = a < p.m;
+    // The lanes beyond the last target go along with it and write nothing, so that
+    // a wavefront takes its branches as one and its search's state stays scalar
+    // (N = 65536, D = 512: 23.9 -> 23.7 ms; the adaptive kernels spilled 4 registers).
+    const bool active = a < p.m, wave_on = a0 < p.m;
+    const int64_t ac = active ? a : p.m - 1;
     // sources j0 .. j0 + nj - 1
     const int64_t j0 = (int64_t)split * p.src_per_split;
     const int nj = (int)max((int64_t)0, min(p.n_src - j0, p.src_per_split));
@@ -315,16 +323,16 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     double3 vt = make_double3(0.0, 0.0, 0.0);  // target's present velocity (adaptive step)
     double eta_min = __longlong_as_double((long long)kPosInfBits), dv2_max = 0.0;
     int32_t self = -1;  // source left out (sources number at most 2^31)
-    if (active) {
+    if (wave_on) {
         if (p.x) {
-            rx = p.x[a];
-            ry = p.x[p.x_stride + a];
-            rz = p.x[2 * p.x_stride + a];
+            rx = p.x[ac];
+            ry = p.x[p.x_stride + ac];
+            rz = p.x[2 * p.x_stride + ac];
             // (an index that names no source leaves none out)
-            const int64_t out = p.self_index ? p.self_index[a] : -1;
+            const int64_t out = p.self_index ? p.self_index[ac] : -1;
             self = out >= 0 && out < p.n_src ? (int32_t)out : -1;
         } else {
-            const int64_t tgt = p.order ? (int64_t)p.order[a] : a;
+            const int64_t tgt = p.order ? (int64_t)p.order[ac] : ac;
             double4 w = p.ring_w[tgt * D + p.head];
             rx = w.x;
             ry = w.y;
@@ -361,7 +369,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     // first (lowest) source of a failing pair; sources number below 2^31
     int32_t fail_j = INT32_MAX;
     const float inv_cdt = (float)(1.0 / (kC_LIGHT * p.dt));
-    const int64_t grp_index = a >> p.g_shift;  // surrogate group of this target
+    const int64_t grp_index = ac >> p.g_shift;  // surrogate group of this target
 
     // LDS: the tile buffers, then the light distance L(b) = c (t - T_b) of
     // every logical slot (shared by all sources).  A buffer holds its TS * D
@@ -478,10 +486,10 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
     }
     // previous-step bracket of this wavefront's next source (warm start)
     uint16_t knext = kBracketBefore;
-    auto load_bracket = [&](int i) { knext = active && i < nj ? p.kc[(j0 + i) * p.m + a] : kBracketBefore; };
+    auto load_bracket = [&](int i) { knext = wave_on && i < nj ? p.kc[(j0 + i) * p.m + ac] : kBracketBefore; };
     if (GUESS == 4)
         load_bracket(sg);
-    int miss_run = 0, bisect_left = 0;
+    int miss_run = 0, bisect_left = 0, bisect_run = kBisectRun;
     int cb = 0;
     for (int i0 = 0; i0 < nj; i0 += TS) {
         if (DB) {
@@ -504,8 +512,8 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
             const uint16_t kcur = knext;
             if (GUESS == 4)
                 load_bracket(s + SG < ns ? i0 + s + SG : i0 + TS + sg);
-            if (active) {
-                if (KSTAR && j == self)
+            if (wave_on) {
+                if (KSTAR && active && j == self)
                     p.kstar[a * p.n_src + jt] = 0;
                 // LDS byte address of the source's first record (its first half)
                 const uint32_t src0 =
@@ -608,10 +616,14 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                                                        __builtin_amdgcn_rcpf(S + __builtin_amdgcn_sqrtf(__builtin_fmaf(
                                                                                      S, S, -4.0f * curv * F))));
                             }
-                            if (any_lane(miss) && ++miss_run >= kMissRun)
-                                bisect_left = kBisectRun;
+                            if (any_lane(miss) && ++miss_run >= kMissRun) {
+                                bisect_left = bisect_run;
+                                if (GUESS != 4)
+                                    bisect_run = min(2 * bisect_run, kBisectMost);
+                            }
                         } else {
                             miss_run = 0;
+                            bisect_run = kBisectRun;
                         }
                     } else {
                         --bisect_left;
@@ -620,26 +632,49 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         miss = true;
                     }
                     if (any_lane(miss)) {
-                        // The paper's search: the oldest sample, then the
-                        // halvings of the whole history, their widths uniform
-                        // across lanes (extra halvings of a one-step bracket
-                        // change nothing).
-                        const bool in_hist = test(D - 1);
+                        // The paper's search: the halvings of the whole history,
+                        // their widths uniform across lanes (extra halvings of a
+                        // one-step bracket change nothing); out of history the
+                        // bracket ends at the oldest sample, which is not in.  A
+                        // wavefront whose first halvings all ran to the oldest end
+                        // tests that sample and may be done.  Bound by LDS reads:
+                        // steps on a curving history (N = 65536, D = 512) took 36.9
+                        // ms with the oldest sample tested first, both of the
+                        // bracket's samples read again and runs of 30, 34.5 now;
+                        // D = 128 over a quarter of the time, half of the pairs
+                        // before it, 28.9 and 26.2 (28.2 with whole batches of
+                        // three halvings, 9 where 7 do).  A count of the sources
+                        // out of history that puts the oldest sample first where
+                        // they are many: 35.4 on the first, 26.5.
                         uint32_t xo = src0;  // f(xo) <= 0, the bracket lies in (xo, xo + n]
-                        if (any_lane(in_hist & other)) {
-                            int n = D - 1;
-                            do {
+                        int n = D - 1;
+                        auto halve = [&](auto times) {
 #pragma unroll
-                                for (int k = 0; k < 3; ++k) {
-                                    const int half = n >> 1;
-                                    const uint32_t mo = xo + (uint32_t)half * (uint32_t)sizeof(double2);
-                                    double3 d;
-                                    xo = value_at(mo, d) > 0.0 ? xo : mo;
-                                    n -= half;
-                                }
-                            } while (n > 1);
+                            for (int k = 0; k < (int)times; ++k) {
+                                const int half = n >> 1;
+                                const uint32_t mo = xo + (uint32_t)half * (uint32_t)sizeof(double2);
+                                double3 d;
+                                xo = value_at(mo, d) > 0.0 ? xo : mo;
+                                n -= half;
+                            }
+                        };
+                        halve(std::integral_constant<int, 3>{});
+                        if (any_lane(other & (xo != addr(D - 1 - n))) || any_lane(other & test(D - 1))) {
+                            while (n > 4)
+                                halve(std::integral_constant<int, 3>{});
+                            while (n > 1)
+                                halve(std::integral_constant<int, 1>{});
+                        } else {
+                            xo = addr(D - 2);
                         }
-                        bracket_at(in_hist ? (int)((xo - src0) / (uint32_t)sizeof(double2)) + 1 : D - 1);
+                        g = (int)((xo - src0) / (uint32_t)sizeof(double2)) + 1;
+                        q1 = value_at(addr(g), d1);
+                        // the newer end's value matters at the newest sample alone
+                        q0 = -1.0;
+                        if (any_lane(g == 1)) {
+                            double3 d;
+                            q0 = value_at(src0, d);
+                        }
                     }
                     before = !(q1 > 0.0);
                 }
@@ -674,7 +709,7 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                     ok = lw_pair_mixed<GUESS == 0>(Ls[g], MixedPair{d1, make_double4(u0.x, u0.y, u3.y, u3.x),
                                                                    make_double4(w0.x, w0.y, w3.y, 0.0)},
                                                    before, (float)p.kq, f, resc);
-                    if (COUNT && valid)
+                    if (COUNT && valid && active)
                         nresc += resc ? 1 : 0;
                     if (valid && ok) {
 #pragma unroll
@@ -721,14 +756,14 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                 if (any_lane(failed) && failed)
                     fail_j = min(fail_j, j);
                 // (kept out of the way of the loads: their wait is in order)
-                if (GUESS >= 4 && valid) {
+                if (GUESS >= 4 && valid && active) {
                     const uint16_t k = before ? kBracketBefore : (uint16_t)g;
                     if (GUESS == 5 || k != kcur)
                         p.kc[jt * p.m + a] = k;
                 }
-                if (KSTAR && valid)
+                if (KSTAR && valid && active)
                     p.kstar[a * p.n_src + jt] = before ? -1 : g;
-                if (COUNT && valid) {
+                if (COUNT && valid && active) {
                     npairs += 1;
                     nbefore += before ? 1 : 0;
                     probes += n_tests;
