@@ -41,8 +41,11 @@ GUESS_NAMES = ["bisect", "mlp", "ballistic", None, "previous"]
 # The roofline's algorithmic work per pair: the plain path's estimate of the
 # measurement plan (about 10 sign tests of 11 flops, 33 for the quadratic,
 # 22 for the reconstruction, 80 for the LW terms, 6 for the sum, in history;
-# 2 sign tests and no acceleration terms before it; the workload's mix).
+# 2 sign tests and no acceleration terms before it; the workload's mix).  It is
+# the method's work, not the pass's: every timed pass confirms a guessed bracket
+# with PASS_PROBES sign tests (pass_flops_per_pair and pass_frac of the line).
 ROOFLINE_FLOP_PER_PAIR = 220.0
+PASS_PROBES = 2
 FLOP_INRING = 32 + 20 + 69 + 6
 FLOP_BEFORE = 32 + 6 + 48 + 6
 
@@ -181,7 +184,8 @@ def run_path(wl, r, u, precision, guess, steps, warmup, train_epochs=2, group_lo
     ctx.set_mode(precision, guess)
     if guess == 4:
         ctx.step(1)  # the first step bisects and fills the bracket cache
-    # one counting step (untimed) for the algorithmic work per launch
+    # one counting step (untimed) for the algorithmic work per launch: sign
+    # tests are those of the mode's plain search, which a counting launch runs
     ctx.set_counting(True)
     ctx.step(1)
     cnt = ctx.counters()
@@ -409,6 +413,9 @@ def main():
     n = wl.bunch.n
     pairs = n * (n - 1)
     achieved = ROOFLINE_FLOP_PER_PAIR * pairs / (ref["pair_kernel_ms"] * 1e-3) / 1e12
+    own, before = None, ref.get("before_history_fraction")
+    if before is not None:
+        own = FLOP_PROBE * PASS_PROBES + FLOP_INRING * (1.0 - before) + FLOP_BEFORE * before
     traffic = measured_traffic() if wl is bunch.C3 else {}
     for x in results:
         tb = traffic.get(x["spec"])
@@ -436,6 +443,11 @@ def main():
                                 f"pair kernel of the {ref['spec']} path"),
                      "flops_per_pair": ROOFLINE_FLOP_PER_PAIR, "counted_flops_per_pair": ref["flops_per_pair"],
                      "launch_ms": ref["pair_kernel_ms"],
+                     # the same with the operations of the pass as it runs (a guess
+                     # confirmed by two sign tests)
+                     "pass_flops_per_pair": own,
+                     "pass_frac": own * pairs / (ref["pair_kernel_ms"] * 1e-3) / 1e12 / PEAK_FP64_VECTOR_TFLOPS
+                     if own else None,
                      # counted HBM bytes over the measured launch time, against 8 TB/s
                      "hbm_gbs": tplain / (ref["pair_kernel_ms"] * 1e-3) / 1e9 if tplain else None,
                      "hbm_frac": tplain / (ref["pair_kernel_ms"] * 1e-3) / 1e9 / PEAK_HBM_GBS if tplain else None,

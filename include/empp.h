@@ -263,7 +263,9 @@ typedef struct {
     double pair_ms;        /* summed duration of pair-kernel launches (ms)   */
     int64_t pair_launches;
     double push_ms;        /* summed duration of push-kernel launches (ms)   */
-    int64_t push_launches;
+    int64_t push_launches; /* one a step of empp_step (its merge and push);
+                              transport: one a step, or one for up to 4096
+                              steps that run in one launch                  */
     double guess_ms;       /* summed duration of surrogate-guess launches    */
     int64_t guess_launches;
 } empp_timing;

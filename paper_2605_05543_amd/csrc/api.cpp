@@ -189,8 +189,10 @@ struct PairSplit {
 // chunks (252 blocks) 74.7, 96 (288 blocks) 117; N = 8192, 32 chunks (256
 // blocks) 417, 256 500, 512 (the nominal chunks) 621; N = 16384, 16 chunks
 // 1588, 256 1773.  ms: N = 40000, D = 256, 16 chunks (640 blocks) 10.0, 64 8.40;
-// N = 65536, 64 chunks of 1024 sources 24.29, 128 of 512 23.87.  64 targets of
-// 8192 sources, 256 chunks: one wavefront 51 us, four 38.5.
+// N = 65536, 64 chunks 24.17, 104 (which the rule takes) 23.83, 128 23.75; warm
+// start, whose layout has 64 rows, 16 chunks 27.41, 24 (taken) 26.98, 64 26.95, and
+// N = 32768, D = 1024, 16 chunks 9.03, 32 (taken) 8.05, 64 8.01.  64 targets of 8192
+// sources, 256 chunks: one wavefront 51 us, four 38.5.
 //
 // In mixed precision the FP32 sums of a target are merged where the nominal
 // chunks end and after every 8 sources from there, whatever the launch's

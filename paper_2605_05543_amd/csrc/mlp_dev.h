@@ -65,13 +65,13 @@ struct TrainRun {
     int64_t count;     // rows available
     int32_t batch;     // rows per optimizer step
     int32_t steps;     // optimizer steps of this launch
-    int32_t row_blocks;  // blocks with rows (the others only share phase 2)
+    int32_t row_blocks;  // blocks with rows: phase 2 sums their partials (the others write zeros)
     int64_t step0;     // index of the launch's first step within the run
     int64_t total;     // steps of the run (learning-rate schedule)
     int64_t adam0;     // Adam steps taken before this launch
     double lr, lr_final;
     int32_t apply;     // 0: one gradient evaluation, no update
-    float *part;       // [row_blocks][kPartStride]
+    float *part;       // [blocks of the launch][kPartStride]
     float *grad;       // [kParams + 1]: summed gradient, then the sum of squared residuals
     float *master, *m, *v;
     float *loss_first; // the run's first sum of squared residuals
