@@ -561,14 +561,16 @@ __device__ __forceinline__ bool grid_barrier(unsigned long long *sync, unsigned 
             __hip_atomic_store(&sync[blockIdx.x], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         meanwhile();
-        unsigned spins = 0;
+        unsigned spins = 0, look = min(polls, 255u);  // a look beyond the slot every 256 polls
         for (int b = threadIdx.x; b < (int)gridDim.x; b += 64) {
             while (__hip_atomic_load(&sync[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
-                if (++spins > polls || ((spins & 255) == 0 &&
-                                        __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
-                    atomicOr(fail, 1u);
-                    lost = 1;
-                    break;
+                if (spins++ >= look) {
+                    if (spins > polls || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                        atomicOr(fail, 1u);
+                        lost = 1;
+                        break;
+                    }
+                    look += 256;
                 }
                 __builtin_amdgcn_s_sleep(1);
             }

@@ -505,18 +505,19 @@ __device__ inline double wait_for_minima(const unsigned long long *slots, unsign
     double v = __longlong_as_double((long long)kPosInfBits);
     if (threadIdx.x < gridDim.x) {
         unsigned long long x;
-        unsigned spins = 0;
-        bool lost = false;
+        unsigned spins = 0, look = min(polls, 255u);  // a look beyond the slot every 256 polls
         while (((x = __hip_atomic_load(&slots[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 63) != tag) {
-            lost = ++spins > polls || ((spins & 255) == 0 &&
-                                       __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0);
-            if (lost) {
-                atomicOr(fail, 1ull);
-                break;
+            if (__builtin_expect(++spins > look, 0)) {
+                if (spins > polls || __hip_atomic_load(fail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                    atomicOr(fail, 1ull);
+                    look = 0;
+                    break;
+                }
+                look += 256;
             }
             __builtin_amdgcn_s_sleep(1);
         }
-        v = lost ? -1.0 : __longlong_as_double((long long)(x & ~(1ull << 63)));
+        v = spins > look ? -1.0 : __longlong_as_double((long long)(x & ~(1ull << 63)));
     }
     const int w = threadIdx.x >> 6;
     if (w < kTransportBlocks / 64) {
