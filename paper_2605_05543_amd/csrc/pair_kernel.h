@@ -22,8 +22,8 @@
 // modes.  MIX selects the mixed-precision field evaluation (root,
 // reconstruction and LW terms in FP32 around FP64 coefficients).
 //
-// What bounds it: vector issue (137 instructions per wavefront and pair at
-// N = 65536, D = 512, the VALU busy 69 % of the time), the vector L1 (three
+// What bounds it: vector issue (132 instructions per wavefront and pair at
+// N = 65536, D = 512, the VALU busy 67 % of the time), the vector L1 (three
 // 16-byte gathers of a lane's segment and the tile's loads) and the latency
 // of a pair's chain (LDS reads of the confirming samples, the gather from L2,
 // about 70 dependent FP64 instructions) on four wavefronts per SIMD.
@@ -34,9 +34,12 @@
 // and the root's square root reused as eta . v', 26.1 ms).  Positions are
 // staged as they are and tested as L^2 - |r - w|^2, velocities gathered from
 // planes and the guess's data made by the push: 23.7 ms (26.1 before), warm
-// start 26.8 (30.8), mixed straight-line 25.9 (27.4), D = 1024 28.5 (31.0);
-// a curving history that bisects pays nine instructions a probe instead of
-// six (N = 16384: 2.63 ms, 2.55 before).
+// start 26.8 (30.8), mixed straight-line 25.9 (27.4), D = 1024 28.5 (31.0).  A
+// curving history that bisects pays nine instructions a probe instead of six,
+// which the leaner field algebra repays in FP64 and mixed precision does not have
+// (a turn of 1.5 rad over the history, with the unrolled bisection and now: FP64,
+// N = 16384 2.61 and 2.39 ms, N = 65536 34.9 and 34.4; mixed 2.57 and 2.41, 34.1 and
+// 35.6).
 #pragma once
 
 #include "pair_common.h"
