@@ -193,7 +193,9 @@ empp_status empp_init_history_straight(empp_ctx *ctx);
  * arrays, nslots == D, oldest first, T strictly increasing) and the
  * present proper velocities u[3][N].  The present time is T[nslots-1];
  * later steps advance it by dt.  EINVAL when a stored speed is >= c or a
- * value is not finite.                                                    */
+ * value is not finite.  The positions must move slower than light too (not
+ * checked): a pair's bracket is unique only then, and a search returns one
+ * of several otherwise.                                                   */
 empp_status empp_set_history(empp_ctx *ctx, int32_t nslots, const double *T, const double *w,
                              const double *v, const double *u);
 
