@@ -38,8 +38,8 @@
 // curving history that bisects pays nine instructions a probe instead of six,
 // which the leaner field algebra repays in FP64 and mixed precision does not have
 // (a turn of 1.5 rad over the history, with the unrolled bisection and now: FP64,
-// N = 16384 2.61 and 2.39 ms, N = 65536 34.9 and 34.4; mixed 2.57 and 2.41, 34.1 and
-// 35.6).
+// N = 16384 2.61 and 2.39 ms, N = 65536 34.9 and 34.1; mixed 2.57 and 2.41, 34.1 and
+// 35.1).
 #pragma once
 
 #include "pair_common.h"
@@ -647,33 +647,37 @@ __device__ __forceinline__ void pair_body(const PairParams &p)
                         // tests that sample and may be done.  Bound by LDS reads:
                         // steps on a curving history (N = 65536, D = 512) took 36.9
                         // ms with the oldest sample tested first, both of the
-                        // bracket's samples read again and runs of 30, 34.5 now;
+                        // bracket's samples read again and runs of 30, 34.2 now;
                         // D = 128 over a quarter of the time, half of the pairs
-                        // before it, 28.9 and 26.2 (28.2 with whole batches of
+                        // before it, 28.9 and 25.9 (28.2 with whole batches of
                         // three halvings, 9 where 7 do).  A count of the sources
                         // out of history that puts the oldest sample first where
-                        // they are many: 35.4 on the first, 26.5.
+                        // they are many: 35.4 on the first, 26.5.  One loop for
+                        // the first batch and the others keeps the kernel short:
+                        // written out twice 34.5 and 26.1, and a step of 256
+                        // particles, which fetches its code anew, 14.9 us for 14.6.
                         uint32_t xo = src0;  // f(xo) <= 0, the bracket lies in (xo, xo + n]
                         int n = D - 1;
-                        auto halve = [&](auto times) {
-#pragma unroll
-                            for (int k = 0; k < (int)times; ++k) {
-                                const int half = n >> 1;
-                                const uint32_t mo = xo + (uint32_t)half * (uint32_t)sizeof(double2);
-                                double3 d;
-                                xo = value_at(mo, d) > 0.0 ? xo : mo;
-                                n -= half;
-                            }
+                        auto halve = [&]() {
+                            const int half = n >> 1;
+                            const uint32_t mo = xo + (uint32_t)half * (uint32_t)sizeof(double2);
+                            double3 d;
+                            xo = value_at(mo, d) > 0.0 ? xo : mo;
+                            n -= half;
                         };
-                        halve(std::integral_constant<int, 3>{});
-                        if (any_lane(other & (xo != addr(D - 1 - n))) || any_lane(other & test(D - 1))) {
-                            while (n > 4)
-                                halve(std::integral_constant<int, 3>{});
-                            while (n > 1)
-                                halve(std::integral_constant<int, 1>{});
-                        } else {
-                            xo = addr(D - 2);
+                        for (bool first = true;; first = false) {
+#pragma unroll
+                            for (int k = 0; k < 3; ++k)
+                                halve();
+                            if (first && !any_lane(other & (xo != addr(D - 1 - n))) && !any_lane(other & test(D - 1))) {
+                                xo = addr(D - 2);
+                                n = 1;
+                            }
+                            if (n <= 4)
+                                break;
                         }
+                        while (n > 1)
+                            halve();
                         g = (int)((xo - src0) / (uint32_t)sizeof(double2)) + 1;
                         q1 = value_at(addr(g), d1);
                         // the newer end's value matters at the newest sample alone
